@@ -332,7 +332,11 @@ void vibe_exec_destroy(vibe_exec* ex); /* synchronises the device first; NULL ac
  *                   lets more reside and the launch has more work items
  *                   than reside with the bitmap in LDS (a small batch is
  *                   bound by its serial chains, which the global masks
- *                   lengthen).  Not with the slab in LDS.
+ *                   lengthen).  Not with the slab in LDS.  FP32 graphs on
+ *                   the serial schedule whose rows are long run an item
+ *                   body with one row state per check and a mask of
+ *                   decisions per chunk (one shot per wavefront, slab in
+ *                   global memory): there this setting changes nothing.
  * A launch whose work items all reside at once (no more than the grid)
  * runs a variant that loads more chunks ahead at fewer wavefronts per SIMD
  * (FP32, serial schedule, slab in global memory, one shot per wavefront,

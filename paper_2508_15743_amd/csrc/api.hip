@@ -71,7 +71,7 @@ size_t carve_sizes(const DevGraph& g, uint32_t bc, bool decode, int slab_blocks,
         decode ? 8ull * bc * g.n : 0,                      // qfix
         4ull * bc,                                         // fail_list
         64,                                                // counters
-        msg_bytes(g) * bp_slabs(g) * slab_blocks * std::max<size_t>((size_t)g.max_chunks * kWave, 1),  // slabs
+        msg_bytes(g) * bp_slabs(g) * slab_blocks * std::max<size_t>(bp_slab_elems(g), 1),  // slabs
         msg_bytes(g) * post_blocks * bp_post_elems(g),     // posterior slabs
         decode ? lsd_scratch_per_block(g) * lsd_grid : 0,  // LSD scratch
     };
@@ -310,7 +310,7 @@ int decode_batch(vibe_graph* G, const uint8_t* bytes, const uint64_t* words, uin
         u = static_cast<uint8_t*>(G->ws_in.base);
     }
     const bool in_lds = use_lds_slab(G, g);
-    if (in_lds) g.dec_global = 0;  // the LDS slab variant keeps decisions in LDS
+    if (in_lds) g.dec_global = g.compact = 0;  // the LDS slab variant keeps decisions in LDS
     const int bpg = G->tune_grid > 0 ? std::min(G->tune_grid, bp_grid(g, in_lds)) : bp_grid(g, in_lds);
     const int lg = lsd_grid_for(bc);
     ChunkBufs W;
@@ -358,10 +358,10 @@ extern "C" int vibe_decode_plain(vibe_graph* G, const uint8_t* syndromes, uint64
     if (B && (!corrections || (!observables && G->h.k))) return fail(VIBE_EINVAL, "an output pointer is NULL");
     if (!B) return VIBE_OK;
     hipStream_t st = static_cast<hipStream_t>(stream);
-    const DevGraph& g = G->h.dg;
+    const bool in_lds = bp_slab_fits_lds(G->h.dg);
+    const DevGraph g = in_lds ? G->h.dg : compact_view(G->h.dg);
     ChunkBufs W;
     const int blocks = (int)g.L;  // one block per member of the one shot
-    const bool in_lds = bp_slab_fits_lds(g);
     if ((rc = carve(g, G, 1, true, in_lds ? 0 : blocks, blocks, 1, &W))) return rc;
     for (uint64_t s0 = 0; s0 < B; s0++) {
         if ((rc = decode_chunk(G, g, W, syndromes, s0, 1, corrections, stats, blocks, 1, st, in_lds))) return rc;
@@ -380,9 +380,9 @@ extern "C" int vibe_bp_ensemble(vibe_graph* G, const uint8_t* syndromes, uint64_
     if (B && !t_conv) return fail(VIBE_EINVAL, "t_conv is NULL");
     if (!B) return VIBE_OK;
     hipStream_t st = static_cast<hipStream_t>(stream);
-    const DevGraph& g = G->h.dg;
+    const bool in_lds = bp_slab_fits_lds(G->h.dg);
+    const DevGraph g = in_lds ? G->h.dg : compact_view(G->h.dg);
     const uint32_t bc = chunk_for(g, B, false);
-    const bool in_lds = bp_slab_fits_lds(g);
     const int bpg = bp_grid(g, in_lds);
     ChunkBufs W;
     if ((rc = carve(g, G, bc, false, in_lds ? 0 : bpg, bpg, 0, &W))) return rc;
@@ -414,6 +414,8 @@ extern "C" int vibe_bp_ensemble(vibe_graph* G, const uint8_t* syndromes, uint64_
         b.post_slab = W.post_slab;
         b.counter = W.counters;
         b.grid = (int)std::min<uint64_t>((uint64_t)bpg, (uint64_t)n * g.L);
+        // every item resident at once: the deeper prefetch ring pays
+        b.latency = (uint64_t)n * g.L <= (uint64_t)std::min(bpg, bp_latency_grid(g, in_lds)) ? 1 : 0;
         if ((rc = launch_bp(g, b, st))) return rc;
     }
     return VIBE_OK;
@@ -492,7 +494,7 @@ int scratch_for_device(int dev, unsigned char** out) {
 // each and one shot fit.
 bool noalloc_plan(const DevGraph& g, bool in_lds, int full_grid, uint64_t B, size_t cap, int* bpg, int* lg,
                   uint32_t* bc, size_t* sizes) {
-    const size_t slab = in_lds ? 0 : msg_bytes(g) * bp_slabs(g) * std::max<size_t>((size_t)g.max_chunks * kWave, 1);
+    const size_t slab = in_lds ? 0 : msg_bytes(g) * bp_slabs(g) * std::max<size_t>(bp_slab_elems(g), 1);
     const size_t per_block = al256(slab) + al256(msg_bytes(g) * bp_post_elems(g));
     const size_t per_lsd = lsd_scratch_per_block(g);
     int grid = (int)std::min<size_t>((size_t)full_grid, (cap / 2) / per_block);
@@ -524,17 +526,25 @@ extern "C" int vibe_decode_noalloc(vibe_graph* G, const uint8_t* syndromes, uint
     if (rc) return rc;
     if (B && (!corrections || (!observables && G->h.k))) return fail(VIBE_EINVAL, "an output pointer is NULL");
     if (!B) return VIBE_OK;
-    DevGraph g = decode_view(G, true, B);
-    const bool in_lds = use_lds_slab(G, g);
-    if (in_lds) g.dec_global = 0;  // the LDS slab variant keeps decisions in LDS
-    const int full = G->tune_grid > 0 ? std::min(G->tune_grid, bp_grid(g, in_lds)) : bp_grid(g, in_lds);
+    DevGraph g;
+    bool in_lds = false;
     int bpg = 0, lg = 0;
     uint32_t bc = 0;
     size_t sizes[kBufs];
-    if (!noalloc_plan(g, in_lds, full, B, kNoallocBytes, &bpg, &lg, &bc, sizes))
+    auto plan = [&](bool compact) {
+        g = decode_view(G, true, B, compact);
+        in_lds = use_lds_slab(G, g);
+        if (in_lds) g.dec_global = g.compact = 0;  // the LDS slab variant keeps decisions in LDS
+        const int full = G->tune_grid > 0 ? std::min(G->tune_grid, bp_grid(g, in_lds)) : bp_grid(g, in_lds);
+        return noalloc_plan(g, in_lds, full, B, kNoallocBytes, &bpg, &lg, &bc, sizes);
+    };
+    // the compact item body needs about a quarter more per block: what the
+    // array holds is judged by the general one, which runs where only it fits
+    if (!plan(false))
         return fail(VIBE_EUNSUPPORTED, "the graph needs more buffer space than the " +
                                            std::to_string(kNoallocBytes >> 20) +
                                            " MiB static scratch of vibe_decode_noalloc holds for one shot");
+    if (!plan(true)) (void)plan(false);
     unsigned char* base = nullptr;
     if ((rc = scratch_for_device(G->device, &base))) return rc;
     ChunkBufs W;

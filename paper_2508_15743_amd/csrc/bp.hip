@@ -31,8 +31,9 @@
 // in global memory: a mask per chunk read with the chunk's slots, and a
 // bitmap updated on flips); convergence is a ballot.
 //
-// Launch variants (none changes a result): the slab in LDS for small
-// graphs; P = 2 or 4 shots of a member per wavefront on the member's
+// Launch variants (none changes a result): compact suffix states, the FP32
+// item body of graphs whose rows are long (bp_compact.h); the slab in LDS
+// for small graphs; P = 2 or 4 shots of a member per wavefront on the member's
 // schedule recut into chunks of 64 / P edges; several requests on
 // different graphs in one persistent launch (ragged); and, for a launch
 // whose items all reside at once, the deeper prefetch ring at four waves
@@ -1030,6 +1031,8 @@ __device__ __forceinline__ void run_group(const DevGraph& g, const BpLaunch& a, 
     }
 }
 
+#include "bp_compact.h"
+
 // Pass context fields that depend only on the block: lane offsets, the
 // block's global slabs and posterior area.
 template <class F>
@@ -1075,6 +1078,61 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(D > kDept
         const uint32_t item = wave_ticket(a.counter, 1u);
         if (item >= n_items) break;
         run_item<F, SLAB_LDS, FLOOD, LAYERED, DG, D>(g, a, item, lds, x);
+        __syncthreads();
+    }
+}
+
+// One launch over the items of one request with compact suffix states.
+//
+// What bounds it.  A launch with many items moves 8 bytes of messages and 2
+// of records per edge and iteration at the rate that this mix of 1-KB reads
+// and writes reaches (4.5 TB/s by the counters; a plain copy 4.6-5.1): the
+// d = 9 circuit graph, 4096 shots, 315 ms, against 455 ms for the general
+// body, which moves 16.  64-byte records and 256-byte chunks one at a time
+// took 345 ms; without the streaming policy on the slab (which keeps the
+// schedule in the L2) 355.  16 to 24 wavefronts per CU run alike, 12 take
+// 345, so the registers go to four groups loaded ahead, at four wavefronts
+// per SIMD.  A launch whose items all reside is bound by the chain of LDS
+// reads, shuffles and sums from chunk to chunk: 304 ns per chunk for both
+// passes (general body: 635), 318 with two groups ahead, where the slab's
+// latency shows.
+template <int DC>
+__global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(4))) void bp_compact_kernel(DevGraph g, BpLaunch a) {
+    extern __shared__ __align__(16) unsigned char lds[];
+    const uint32_t slab_elems = bp_slab_elems(g);
+    const Rsrc slb = make_rsrc(reinterpret_cast<uint32_t*>(a.slab) + (size_t)blockIdx.x * slab_elems, slab_elems * 4u);
+    float* post = reinterpret_cast<float*>(a.post_slab) + (size_t)blockIdx.x * bp_post_elems(g);
+    const uint32_t n_items = a.n_shots * g.L;
+    for (;;) {
+        const uint32_t item = wave_ticket(a.counter, 1u);
+        if (item >= n_items) break;
+        run_item_c<DC>(g, a, item, lds, slb, post);
+        __syncthreads();
+    }
+}
+
+// The ragged launch with compact suffix states: FP32, every segment on the
+// serial schedule with one shot per wavefront and its slab in global memory;
+// segments whose graph has no compact data run the general item body.
+template <int DC>
+__global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(4))) void bp_ragged_compact_kernel(RaggedLaunch r) {
+    using CSeg = const __attribute__((address_space(4))) BpSeg;
+    extern __shared__ __align__(16) unsigned char lds[];
+    CSeg* segs = (CSeg*)r.segs;
+    uint32_t* gslab = reinterpret_cast<uint32_t*>(r.slab) + (size_t)blockIdx.x * r.slab_elems;
+    float* post = reinterpret_cast<float*>(r.post_slab) + (size_t)blockIdx.x * r.post_elems;
+    const Ctx<float> x = block_ctx<float>(gslab, nullptr, r.slab_elems, post);
+    for (;;) {
+        const uint32_t item = wave_ticket(r.counter, 1u);
+        if (item >= r.n_items) break;
+        uint32_t j = 0;
+        while (j + 1 < r.n_segs && segs[j + 1].item0 <= item) j++;
+        const DevGraph g = load_const(&r.segs[j].g);
+        const BpLaunch a = load_const(&r.segs[j].a);
+        if (g.compact)
+            run_item_c<DC>(g, a, item - segs[j].item0, lds, x.slb, post);
+        else
+            run_item<float, false, false, false, false, kDepth>(g, a, item - segs[j].item0, lds, x);
         __syncthreads();
     }
 }
@@ -1214,7 +1272,11 @@ const void* multi_kernel_for(bool ragged, uint32_t P) {
 // several shots per wavefront; dg: decisions in global memory (the
 // non-layered items; the slab in global memory)
 const void* kernel_for(bool fp64, bool flood, bool slab_in_lds, bool ragged, bool layered = false, uint32_t P = 1,
-                       bool dg = false, bool latency = false) {
+                       bool dg = false, bool latency = false, int compact = 0) {
+    if (compact) {
+        if (ragged) return compact <= 6 ? (const void*)bp_ragged_compact_kernel<6> : (const void*)bp_ragged_compact_kernel<8>;
+        return compact <= 6 ? (const void*)bp_compact_kernel<6> : (const void*)bp_compact_kernel<8>;
+    }
     // the latency variant: FP32, serial schedule, global slab, one shot per
     // wavefront, decisions in LDS
     if (latency && !fp64 && !flood && !slab_in_lds && !layered && P == 1 && !dg)
@@ -1253,6 +1315,10 @@ int bp_slabs(const DevGraph& g) { return g.flood ? 2 : 1; }
 
 size_t bp_lds_bytes(const DevGraph& g, bool slab_in_lds) {
     const size_t mb = g.fp64 ? 8 : 4;
+    // compact: syndrome, residual, two row states per check and for the
+    // dummy check; the decision bitmap is formed over the row states
+    if (g.compact && !slab_in_lds)
+        return 16 * (size_t)g.words_m + 8 * (size_t)bp_compact_rows(g);
     // per shot of the wavefront: syndrome, residual, decisions (unless in
     // global memory: never with the slab in LDS), row states
     const bool dec_lds = slab_in_lds || !g.dec_global;
@@ -1267,7 +1333,7 @@ size_t bp_lds_bytes(const DevGraph& g, bool slab_in_lds) {
 bool bp_slab_fits_lds(const DevGraph& g) { return !g.layered && g.P == 1 && bp_lds_bytes(g, true) <= 96 * 1024; }
 
 int bp_grid_for(bool fp64, bool flood, bool slab_in_lds, size_t lds_bytes, bool ragged, bool layered, uint32_t P,
-                bool dec_global, bool latency) {
+                bool dec_global, bool latency, int compact) {
     // resident blocks of a kernel variant at an LDS size, per device: an
     // occupancy query per launch plan is cheap but not free, so the answers
     // are kept (a few variants and sizes per graph)
@@ -1275,7 +1341,7 @@ int bp_grid_for(bool fp64, bool flood, bool slab_in_lds, size_t lds_bytes, bool 
     static std::map<std::tuple<int, const void*, size_t>, int> cache;
     int dev = 0;
     (void)hipGetDevice(&dev);
-    const void* fn = kernel_for(fp64, flood, slab_in_lds, ragged, layered, P, dec_global, latency);
+    const void* fn = kernel_for(fp64, flood, slab_in_lds, ragged, layered, P, dec_global, latency, compact);
     const auto key = std::make_tuple(dev, fn, lds_bytes);
     std::lock_guard<std::mutex> lk(mu);
     auto it = cache.find(key);
@@ -1296,6 +1362,7 @@ bool use_lds_slab(const vibe_graph* G, const DevGraph& g) {
     if (G->tune_lds > 0) return true;
     DevGraph d = g;
     d.dec_global = 0;
+    d.compact = 0;
     return bp_grid(d, true) >= bp_grid(d, false);
 }
 
@@ -1310,11 +1377,11 @@ bool dec_global_pays(const DevGraph& g) {
 
 int bp_grid(const DevGraph& g, bool slab_in_lds) {
     return bp_grid_for(g.fp64 != 0, g.flood != 0, slab_in_lds, bp_lds_bytes(g, slab_in_lds), false, g.layered != 0,
-                       g.P, g.dec_global != 0);
+                       g.P, g.dec_global != 0, false, slab_in_lds ? 0 : g.compact);
 }
 
 int bp_latency_grid(const DevGraph& g, bool slab_in_lds) {
-    if (g.fp64 || g.flood || g.layered || slab_in_lds || g.P != 1 || g.dec_global) return 0;
+    if (g.fp64 || g.flood || g.layered || slab_in_lds || g.P != 1 || g.dec_global || g.compact) return 0;
     return bp_grid_for(false, false, false, bp_lds_bytes(g, false), false, false, 1, false, true);
 }
 
@@ -1326,11 +1393,14 @@ int launch_bp(const DevGraph& g, const BpLaunch& a, hipStream_t st) {
                                  "and stop on convergence");
     if (g.dec_global && (g.layered || in_lds))
         return fail(VIBE_EINVAL, "internal: decisions in global memory need a chunked schedule and a global slab");
+    if (g.compact && (g.fp64 || g.flood || g.layered || in_lds || g.P != 1 || !g.csched || g.dec_global))
+        return fail(VIBE_EINVAL, "internal: compact suffix states need FP32, the serial schedule, a global slab and "
+                                 "one shot per wavefront");
     if (a.latency && !bp_latency_grid(g, in_lds))
         return fail(VIBE_EINVAL, "internal: the latency variant needs FP32, the serial schedule, a global slab, "
                                  "one shot per wavefront and decisions in LDS");
     return launch_fn(kernel_for(g.fp64 != 0, g.flood != 0, in_lds, false, g.layered != 0, g.P, g.dec_global != 0,
-                                a.latency != 0),
+                                a.latency != 0, g.compact),
                      a.grid, bp_lds_bytes(g, in_lds), args, st);
 }
 
@@ -1344,8 +1414,11 @@ int launch_bp_ragged(const RaggedLaunch& r, hipStream_t st) {
     if (r.latency && (r.fp64 || r.flood || r.slab_in_lds || r.layered || r.multi || r.dec_global))
         return fail(VIBE_EINVAL, "internal: the latency variant needs FP32, the serial schedule, global slabs, "
                                  "one shot per wavefront and decisions in LDS");
+    if (r.compact && (r.fp64 || r.flood || r.slab_in_lds || r.layered || r.multi || r.dec_global))
+        return fail(VIBE_EINVAL, "internal: compact suffix states need FP32, the serial schedule, global slabs and "
+                                 "one shot per wavefront");
     return launch_fn(kernel_for(r.fp64 != 0, r.flood != 0, r.slab_in_lds != 0, true, r.layered != 0,
-                                r.multi ? 2u : 1u, r.dec_global != 0, r.latency != 0),
+                                r.multi ? 2u : 1u, r.dec_global != 0, r.latency != 0, r.compact),
                      r.grid, r.lds_bytes, args, st);
 }
 

@@ -105,6 +105,19 @@ struct DevGraph {
     const uint32_t* member_chunk; // L + 1: chunk range of each member
     const uint32_t* cperm;        // layered schedule: L x m check orders (else unused)
     const uint64_t* lobs;         // k x words_n, bit-packed observable rows
+    // compact suffix states (bp_compact.h); csched is null where the graph has none
+    int compact;                  // launched with the compact item body: the most edges of a
+                                  // column it sums over (6 or 8), or 0
+    int ccols;                    // 6 or 8: what compact is set to
+    uint32_t cgroups;             // largest group count of a member (four chunks each, even)
+    const unsigned char* csched;  // per group: meta[64][4], lambda[64][4].  meta: bits 0-7 four
+                                  // times the column's first lane; bit 8 + q: the column has a
+                                  // position q and this lane is another; bits 18-30 c; bit 31:
+                                  // its last lane.  Unused slots: c = m, their own first lane
+    const unsigned char* crec0;   // per chunk: the record of the initial messages (64 bytes)
+    const uint32_t* crow0;        // m: row states of all initial messages
+    const uint32_t* cgroup;       // L + 1: group range of each member
+    const uint32_t* dense0;       // L: its first group whose states stay in the slab slots (even)
 };
 
 struct GraphHost {
@@ -217,14 +230,15 @@ struct RaggedLaunch {
     int layered;           // some segment is on the layered schedule
     int dec_global;        // the non-layered segments keep decisions in global memory
     int latency;           // the latency variant (every item resident at once)
+    int compact;           // some segment runs the compact item body: the largest DevGraph.compact
     size_t lds_bytes;      // largest bp_lds_bytes over the segments
 };
 int launch_bp_ragged(const RaggedLaunch& r, hipStream_t st);
 int bp_grid_for(bool fp64, bool flood, bool slab_in_lds, size_t lds_bytes, bool ragged, bool layered = false,
-                uint32_t P = 1, bool dec_global = false, bool latency = false);
+                uint32_t P = 1, bool dec_global = false, bool latency = false, int compact = 0);
 // Resident blocks of the latency variant of K1 for g (0 where g has none:
 // FP64, another schedule, slab in LDS, several shots per wavefront,
-// decisions in global memory).
+// decisions in global memory, compact suffix states, which need none).
 int bp_latency_grid(const DevGraph& g, bool slab_in_lds);
 int bp_grid(const DevGraph& g, bool slab_in_lds);
 size_t bp_lds_bytes(const DevGraph& g, bool slab_in_lds);
@@ -244,6 +258,18 @@ __host__ __device__ inline size_t bp_post_elems(const DevGraph& g) {
     if (!g.dec_global) return bp_post_head(g);
     return bp_post_head(g) + ((size_t)g.max_chunks + (size_t)g.P * g.words_n) * (g.fp64 ? 1 : 2);
 }
+// message slab of one BP block (one of bp_slabs), in message-precision
+// elements; with compact suffix states: per group of four chunks the
+// messages, then per group the records, then per chunk a decision mask, in
+// all a multiple of 256 bytes
+__host__ __device__ inline uint32_t bp_slab_elems(const DevGraph& g) {
+    return g.compact ? (g.cgroups * (4 * kWave + 4 * 16 + 4 * 2) + 63) / 64 * 64 : g.max_chunks * kWave;
+}
+// LDS of a compact item body's row states, or of the decision bitmap formed
+// over them, in 8-byte words
+__host__ __device__ inline uint32_t bp_compact_rows(const DevGraph& g) {
+    return g.m + 1 > g.words_n ? g.m + 1 : g.words_n;
+}
 // BP work items of n shots: (member, group of P shots)
 inline uint64_t bp_items(const DevGraph& g, uint64_t n) { return (n + g.P - 1) / g.P * g.L; }
 
@@ -252,7 +278,11 @@ inline uint64_t bp_items(const DevGraph& g, uint64_t n) { return (n + g.P - 1) /
 // 1 (and allow_multi), else the 64-edge schedule; decisions in global memory
 // as tune_dec says (automatic: where that lets more wavefronts reside and
 // the work items outnumber those that reside with decisions in LDS).
-DevGraph decode_view(const vibe_graph* G, bool allow_multi = true, uint64_t shots = UINT64_MAX);
+DevGraph decode_view(const vibe_graph* G, bool allow_multi = true, uint64_t shots = UINT64_MAX,
+                     bool allow_compact = true);
+// d with the compact item body switched on where the graph has its data and
+// runs one shot per wavefront.
+DevGraph compact_view(DevGraph d);
 // Whether decisions in global memory let more BP wavefronts reside than a
 // decision bitmap in LDS (g.dec_global ignored).
 bool dec_global_pays(const DevGraph& g);

@@ -110,6 +110,7 @@ struct Round {
     bool layered = false;  // some segment is on the layered schedule
     bool dec_global = false;  // chunked segments keep decisions in global memory
     bool latency = false;     // every item resident at once: the deeper prefetch ring
+    int compact = 0;          // some segment runs the compact item body
 };
 
 size_t seg_bytes(const DevGraph& g, uint32_t n) {
@@ -135,7 +136,7 @@ int check_requests(const vibe_request* reqs, uint32_t n) {
 
 // Split the requests into rounds whose per-shot buffers fit the budget, and
 // lay out each round's workspace.
-std::vector<Round> plan(const vibe_request* reqs, uint32_t n_reqs, size_t budget) {
+std::vector<Round> plan(const vibe_request* reqs, uint32_t n_reqs, size_t budget, bool allow_compact = true) {
     std::vector<Round> rounds;
     Round cur;
     size_t used = 0;
@@ -201,6 +202,15 @@ std::vector<Round> plan(const vibe_request* reqs, uint32_t n_reqs, size_t budget
             g.dec_global = 0;
             lds_ok = lds_ok && !multi && use_lds_slab(reqs[sg.req].graph, g);
         }
+        // compact suffix states where the launch is one shot per wavefront on
+        // the serial schedule with global slabs and decisions in LDS; the
+        // other launches run every segment on the general item body
+        bool compact_ok = allow_compact && !flood && !layered && !multi && !lds_ok;
+        for (const Seg& sg : r.segs) compact_ok = compact_ok && !sg.g.dec_global;
+        for (Seg& sg : r.segs) {
+            if (!compact_ok) sg.g = decode_view(reqs[sg.req].graph, all_multi, sg.n, false);
+            r.compact = std::max(r.compact, sg.g.compact);
+        }
         // decisions in global memory for every chunked segment if one of
         // them wants it (a graph whose decision bitmap would cap the
         // launch's occupancy); not with LDS slabs, and the launch without
@@ -213,7 +223,7 @@ std::vector<Round> plan(const vibe_request* reqs, uint32_t n_reqs, size_t budget
         for (const Seg& sg : r.segs) {
             const DevGraph& g = sg.g;
             fp64 = g.fp64 != 0;
-            r.slab_elems = std::max<uint32_t>(r.slab_elems, std::max<uint32_t>(g.max_chunks, 1) * kWave);
+            r.slab_elems = std::max<uint32_t>(r.slab_elems, std::max<uint32_t>(bp_slab_elems(g), kWave));
             r.post_elems = std::max<uint32_t>(r.post_elems, (uint32_t)bp_post_elems(g));
             lds_global = std::max(lds_global, bp_lds_bytes(g, false));
             lds_l = std::max(lds_l, bp_lds_bytes(g, true));
@@ -225,7 +235,8 @@ std::vector<Round> plan(const vibe_request* reqs, uint32_t n_reqs, size_t budget
         r.layered = layered;
         r.dec_global = dg;
         r.lds_bytes = lds_ok ? lds_l : lds_global;
-        r.grid = bp_grid_for(fp64, flood, lds_ok, r.lds_bytes, true, layered, multi ? 2u : 1u, r.dec_global);
+        r.grid = bp_grid_for(fp64, flood, lds_ok, r.lds_bytes, true, layered, multi ? 2u : 1u, r.dec_global, false,
+                             r.compact);
         uint64_t total_items = 0, max_n = 0;
         for (const Seg& sg : r.segs) {
             total_items += bp_items(sg.g, sg.n);
@@ -235,7 +246,7 @@ std::vector<Round> plan(const vibe_request* reqs, uint32_t n_reqs, size_t budget
         if (!fp64 && !flood && !lds_ok && !layered && !multi && !dg)
             r.latency = total_items <= (uint64_t)r.grid &&
                         total_items <= (uint64_t)bp_grid_for(false, false, false, r.lds_bytes, true, false, 1u,
-                                                             false, true);
+                                                             false, true, r.compact);
         r.lsd_grid = (int)std::min<uint64_t>(512, std::max<uint64_t>(max_n, 1));
         // layout: [zeroed: counters | per-segment cmask, iters, qfix, fail count]
         //         [per-segment t_conv, weight, cand, fail_list] [segment table]
@@ -336,6 +347,7 @@ int run_round(const vibe_request* reqs, const Round& r, unsigned char* base, hip
     L.layered = r.layered ? 1 : 0;
     L.dec_global = r.dec_global ? 1 : 0;
     L.latency = r.latency ? 1 : 0;
+    L.compact = r.compact;
     L.lds_bytes = r.lds_bytes;
     if ((rc = launch_bp_ragged(L, st))) return rc;
     for (size_t j = 0; j < r.segs.size(); j++) {
@@ -638,7 +650,8 @@ extern "C" int vibe_autotune(vibe_graph* g, const uint8_t* syndromes, uint64_t B
     for (int P : {1, 2, 4})
         if (P == 1 || multi_ok(g, (uint32_t)P))
             for (int dec : {0, 1})
-                if (!d.layered || dec == 0) first.push_back(vibe_launch_t{0, 0, P, dec, 0, 0.0});
+                // the compact item body keeps its decisions one way only
+                if (dec == 0 || (!d.layered && !(P == 1 && compact_view(d).compact))) first.push_back(vibe_launch_t{0, 0, P, dec, 0, 0.0});
     vibe_launch_t best{0, 0, 1, 0, 0, 1e30};
     bool timed = false;
     for (const vibe_launch_t& s : first) {
@@ -656,7 +669,7 @@ extern "C" int vibe_autotune(vibe_graph* g, const uint8_t* syndromes, uint64_t B
     if (!rc) {
         (void)apply_launch(g, best);
         DevGraph v = decode_view(g, true, B);
-        if (best.slab_in_lds) v.dec_global = 0;
+        if (best.slab_in_lds) v.dec_global = v.compact = 0;
         const int full = bp_grid(v, best.slab_in_lds != 0);
         const vibe_launch_t base = best;
         for (int eighths : {7, 6, 5, 4}) {
@@ -786,10 +799,13 @@ struct BatchLayout {
     vibe::Round round;
     size_t synd = 0, corr = 0, obs = 0, stats = 0, tab = 0, bytes = 0;
     bool one_round = false;
+    bool compact = true;  // planned with compact suffix states allowed
 };
 
-BatchLayout batch_layout(vibe_graph* G, uint64_t shots, uint32_t n_req) {
+// compact: whether the round may use compact suffix states (a larger slab).
+BatchLayout batch_layout(vibe_graph* G, uint64_t shots, uint32_t n_req, bool compact) {
     BatchLayout L;
+    L.compact = compact;
     const vibe::DevGraph& g = G->h.dg;
     vibe_request r{};
     r.graph = G;
@@ -797,7 +813,7 @@ BatchLayout batch_layout(vibe_graph* G, uint64_t shots, uint32_t n_req) {
     r.corrections = reinterpret_cast<uint64_t*>(1);
     r.observables = reinterpret_cast<uint8_t*>(1);
     r.B = std::max<uint64_t>(shots, 1);
-    std::vector<vibe::Round> rs = vibe::plan(&r, 1, vibe::kRaggedBudget);
+    std::vector<vibe::Round> rs = vibe::plan(&r, 1, vibe::kRaggedBudget, compact);
     L.one_round = rs.size() == 1;
     L.round = rs[0];
     size_t off = vibe::al256(L.round.bytes);
@@ -813,6 +829,13 @@ BatchLayout batch_layout(vibe_graph* G, uint64_t shots, uint32_t n_req) {
     off += vibe::al256(sizeof(vibe::CopyEntry) * 4ull * std::max<uint32_t>(n_req, 1));
     L.bytes = off;
     return L;
+}
+
+// The layout used in a pool of `pool` bytes: with compact suffix states
+// unless only the general item body's smaller slab fits the pool.
+BatchLayout batch_layout_in(size_t pool, vibe_graph* G, uint64_t shots, uint32_t n_req) {
+    BatchLayout L = batch_layout(G, shots, n_req, true);
+    return L.bytes > pool ? batch_layout(G, shots, n_req, false) : L;
 }
 
 }  // namespace
@@ -911,7 +934,7 @@ void server_loop(vibe_server* S) {
                     upto.push_back(shots);
                 }
                 auto fits = [&](size_t k, BatchLayout* out) {  // the first k candidates
-                    BatchLayout t = batch_layout(G, upto[k - 1], (uint32_t)k);
+                    BatchLayout t = batch_layout_in(S->pool.bytes, G, upto[k - 1], (uint32_t)k);
                     if (out) *out = t;
                     return t.one_round && t.bytes <= room;
                 };
@@ -991,7 +1014,7 @@ void server_loop(vibe_server* S) {
             q.corrections = reinterpret_cast<uint64_t*>(base + lay.corr);
             q.observables = base + lay.obs;
             q.stats = reinterpret_cast<vibe_shot_stats*>(base + lay.stats);
-            std::vector<vibe::Round> rounds = vibe::plan(&q, 1, vibe::kRaggedBudget);
+            std::vector<vibe::Round> rounds = vibe::plan(&q, 1, vibe::kRaggedBudget, lay.compact);
             vibe::CopyEntry* dtab = reinterpret_cast<vibe::CopyEntry*>(base + lay.tab);
             if (rounds.size() != 1 || rounds[0].bytes > lay.round.bytes) {
                 rc = vibe::fail(VIBE_ENOMEM, "internal: a batch outgrew its block");
@@ -1052,9 +1075,9 @@ extern "C" int vibe_server_create(vibe_graph* const* graphs, uint32_t n_graphs, 
         size_t worst = 0;
         for (uint32_t i = 0; i < n_graphs; i++) {
             uint64_t b = cfg->max_batch_shots;
-            BatchLayout L = batch_layout(graphs[i], b, cfg->max_batch_requests);
-            while (!L.one_round && b > 1) L = batch_layout(graphs[i], b /= 2, cfg->max_batch_requests);
-            worst = std::max(worst, L.bytes);
+            BatchLayout L = batch_layout(graphs[i], b, cfg->max_batch_requests, false);
+            while (!L.one_round && b > 1) L = batch_layout(graphs[i], b /= 2, cfg->max_batch_requests, false);
+            worst = std::max({worst, L.bytes, batch_layout(graphs[i], b, cfg->max_batch_requests, true).bytes});
         }
         pool = worst * cfg->slots;
     }
@@ -1116,8 +1139,9 @@ extern "C" int vibe_server_submit(vibe_server* S, uint32_t graph_index, const ui
     int rc = check_requests(&r, 1);
     if (rc) return rc;
     // admission by footprint: the request alone must fit the pool (and one
-    // round of per-shot buffers); it is queued until that much is free
-    const BatchLayout L = batch_layout(r.graph, B, 1);
+    // round of per-shot buffers); it is queued until that much is free.  The
+    // footprint is the general item body's, which can always run it.
+    const BatchLayout L = batch_layout(r.graph, B, 1, false);
     if (!L.one_round) return fail(VIBE_EINVAL, "a request needs more than one round of per-shot buffers");
     if (L.bytes > S->pool.bytes)
         return fail(VIBE_ENOMEM, "the request's footprint (" + std::to_string(L.bytes) +
