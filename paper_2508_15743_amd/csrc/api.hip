@@ -4,7 +4,8 @@
 // wavefront per (shot, member), correction limit applied on the fly, the
 // normalised posteriors of unconverged members accumulated in fixed point),
 // K2 (selection by prior weight; shots with no converged member are queued),
-// K3 (LSD-0 on the queued shots); then K4 (observables) over the whole batch.
+// K3 (LSD-0 on the queued shots); both write the observables of the shots
+// they decide.
 #include <algorithm>
 #include <cstring>
 #include <mutex>
@@ -62,15 +63,17 @@ int ensure_workspace(vibe_graph* G, size_t bytes) {
 constexpr int kBufs = 11;
 size_t carve_sizes(const DevGraph& g, uint32_t bc, bool decode, int slab_blocks, int post_blocks, int lsd_grid,
                    size_t* sizes) {
+    // the buffers a decode starts from zero come first, so that one launch
+    // clears them
     const size_t s[kBufs] = {
+        64,                                                // counters
+        4ull * bc,                                         // iters
+        8ull * bc * (kMaxT + 1),                           // convergence masks
+        decode ? 8ull * bc * g.n : 0,                      // qfix
         4ull * bc * g.L,                                   // t_conv
         decode ? 8ull * bc * g.L : 0,                      // weight
         decode ? 8ull * bc * g.L * g.words_n : 0,          // cand
-        8ull * bc * (kMaxT + 1),                           // convergence masks
-        4ull * bc,                                         // iters
-        decode ? 8ull * bc * g.n : 0,                      // qfix
         4ull * bc,                                         // fail_list
-        64,                                                // counters
         msg_bytes(g) * bp_slabs(g) * slab_blocks * std::max<size_t>(bp_slab_elems(g), 1),  // slabs
         msg_bytes(g) * post_blocks * bp_post_elems(g),     // posterior slabs
         decode ? lsd_scratch_per_block(g) * lsd_grid : 0,  // LSD scratch
@@ -91,14 +94,14 @@ void carve_at(unsigned char* p, const size_t* sizes, ChunkBufs* B) {
         ptrs[i] = sizes[i] ? p : nullptr;
         p += al256(sizes[i]);
     }
-    B->t_conv = (int32_t*)ptrs[0];
-    B->weight = (double*)ptrs[1];
-    B->cand = (uint64_t*)ptrs[2];
-    B->cmask = (uint64_t*)ptrs[3];
-    B->iters = (uint32_t*)ptrs[4];
-    B->qfix = (int64_t*)ptrs[5];
-    B->fail_list = (uint32_t*)ptrs[6];
-    B->counters = (uint32_t*)ptrs[7];
+    B->counters = (uint32_t*)ptrs[0];
+    B->iters = (uint32_t*)ptrs[1];
+    B->cmask = (uint64_t*)ptrs[2];
+    B->qfix = (int64_t*)ptrs[3];
+    B->t_conv = (int32_t*)ptrs[4];
+    B->weight = (double*)ptrs[5];
+    B->cand = (uint64_t*)ptrs[6];
+    B->fail_list = (uint32_t*)ptrs[7];
     B->slab = ptrs[8];
     B->post_slab = ptrs[9];
     B->lsd_scratch = ptrs[10];
@@ -116,23 +119,22 @@ int carve(const DevGraph& g, vibe_graph* G, uint32_t bc, bool decode, int slab_b
     return VIBE_OK;
 }
 
-int lsd_grid_for(uint64_t B) {
-    uint64_t g = std::min<uint64_t>(B ? B : 1, 512);
-    return (int)g;
+// Clears what a launch sequence over n shots counts and accumulates in:
+// everything from the counters to the shots' averages (decode) or masks.
+int clear_counts(const DevGraph& g, const ChunkBufs& W, uint32_t n, bool decode, hipStream_t st) {
+    unsigned char* from = reinterpret_cast<unsigned char*>(W.counters);
+    unsigned char* to = decode ? reinterpret_cast<unsigned char*>(W.qfix + (size_t)n * g.n)
+                               : reinterpret_cast<unsigned char*>(W.cmask + (size_t)n * (kMaxT + 1));
+    return launch_zero(from, (size_t)(to - from), st);
 }
-
-int memset_async(void* p, size_t bytes, hipStream_t st) { return launch_zero(p, bytes, st); }
 
 // One chunk of the decoder: shots [shot0, shot0 + n), on g (the handle's
 // graph, or its view with a recut schedule).
 int decode_chunk(vibe_graph* G, const DevGraph& g, const ChunkBufs& W, const uint8_t* synd, uint64_t shot0,
-                 uint32_t n, uint64_t* corr, vibe_shot_stats* stats, int bp_blocks, int lsd_grid, hipStream_t st,
-                 bool in_lds, bool timed = true) {
+                 uint32_t n, uint64_t* corr, uint8_t* obs, vibe_shot_stats* stats, int bp_blocks, int lsd_grid,
+                 hipStream_t st, bool in_lds, bool timed = true) {
     int rc;
-    if ((rc = memset_async(W.cmask, 8ull * n * (kMaxT + 1), st)) ||
-        (rc = memset_async(W.iters, 4ull * n, st)) || (rc = memset_async(W.qfix, 8ull * n * g.n, st)) ||
-        (rc = memset_async(W.counters, 64, st)))
-        return rc;
+    if ((rc = clear_counts(g, W, n, true, st))) return rc;
     BpLaunch b{};
     b.member_major = 1;
     b.slab_in_lds = in_lds ? 1 : 0;
@@ -170,6 +172,7 @@ int decode_chunk(vibe_graph* G, const DevGraph& g, const ChunkBufs& W, const uin
     s.iters = W.iters;
     s.conv_mask = W.cmask;
     s.corrections = corr;
+    s.observables = obs;
     s.stats = stats;
     s.fail_list = W.fail_list;
     s.fail_count = W.counters + 1;
@@ -185,6 +188,7 @@ int decode_chunk(vibe_graph* G, const DevGraph& g, const ChunkBufs& W, const uin
     l.soft_f32 = nullptr;
     l.soft_fix = W.qfix;
     l.corrections = corr;
+    l.observables = obs;
     l.stats = stats;
     l.scratch = W.lsd_scratch;
     l.scratch_per_block = lsd_scratch_per_block(g);
@@ -277,7 +281,7 @@ namespace vibe {
 namespace {
 
 // The batched decode of vibe_decode (bytes != NULL) and vibe_decode_packed
-// (words != NULL): chunks of shots through K1-K3, then K4 over the batch.
+// (words != NULL): chunks of shots through K1-K3.
 // Packed syndromes are expanded chunk by chunk into the handle's input
 // buffer, and that chunk is then decoded as shots 0..n-1 of it.
 int decode_batch(vibe_graph* G, const uint8_t* bytes, const uint64_t* words, uint64_t B, uint64_t* corrections,
@@ -312,14 +316,14 @@ int decode_batch(vibe_graph* G, const uint8_t* bytes, const uint64_t* words, uin
     const bool in_lds = use_lds_slab(G, g);
     if (in_lds) g.dec_global = g.compact = 0;  // the LDS slab variant keeps decisions in LDS
     const int bpg = G->tune_grid > 0 ? std::min(G->tune_grid, bp_grid(g, in_lds)) : bp_grid(g, in_lds);
-    const int lg = lsd_grid_for(bc);
+    const int lg = lsd_grid_for(lsd_lds_bytes(g), lsd_scratch_per_block(g), bc);
     ChunkBufs W;
     if ((rc = carve(g, G, bc, true, in_lds ? 0 : bpg, bpg, lg, &W))) return rc;
     const uint32_t wm = g.words_m ? g.words_m : 1;
     for (uint64_t s0 = 0; s0 < B; s0 += bc) {
         const uint32_t n = (uint32_t)std::min<uint64_t>(bc, B - s0);
         if (!words) {
-            rc = decode_chunk(G, g, W, bytes, s0, n, corrections, stats, bpg, lg, st, in_lds);
+            rc = decode_chunk(G, g, W, bytes, s0, n, corrections, observables, stats, bpg, lg, st, in_lds);
         } else {
             const uint64_t cells = (uint64_t)n * g.m;
             if (cells) {
@@ -328,12 +332,12 @@ int decode_batch(vibe_graph* G, const uint8_t* bytes, const uint64_t* words, uin
                 hipError_t e = hipGetLastError();
                 if (e != hipSuccess) return hip_fail(e, "unpack_kernel launch");
             }
-            rc = decode_chunk(G, g, W, u, 0, n, corrections + s0 * g.words_n, stats ? stats + s0 : nullptr, bpg,
-                              lg, st, in_lds);
+            rc = decode_chunk(G, g, W, u, 0, n, corrections + s0 * g.words_n, observables + s0 * g.k,
+                              stats ? stats + s0 : nullptr, bpg, lg, st, in_lds);
         }
         if (rc) return rc;
     }
-    return launch_observables(g, corrections, 0, (uint32_t)std::min<uint64_t>(B, UINT32_MAX), observables, st);
+    return VIBE_OK;
 }
 
 }  // namespace
@@ -364,8 +368,8 @@ extern "C" int vibe_decode_plain(vibe_graph* G, const uint8_t* syndromes, uint64
     const int blocks = (int)g.L;  // one block per member of the one shot
     if ((rc = carve(g, G, 1, true, in_lds ? 0 : blocks, blocks, 1, &W))) return rc;
     for (uint64_t s0 = 0; s0 < B; s0++) {
-        if ((rc = decode_chunk(G, g, W, syndromes, s0, 1, corrections, stats, blocks, 1, st, in_lds))) return rc;
-        if ((rc = launch_observables(g, corrections, s0, 1, observables, st))) return rc;
+        if ((rc = decode_chunk(G, g, W, syndromes, s0, 1, corrections, observables, stats, blocks, 1, st, in_lds)))
+            return rc;
     }
     return VIBE_OK;
 }
@@ -388,9 +392,7 @@ extern "C" int vibe_bp_ensemble(vibe_graph* G, const uint8_t* syndromes, uint64_
     if ((rc = carve(g, G, bc, false, in_lds ? 0 : bpg, bpg, 0, &W))) return rc;
     for (uint64_t s0 = 0; s0 < B; s0 += bc) {
         const uint32_t n = (uint32_t)std::min<uint64_t>(bc, B - s0);
-        if ((rc = memset_async(W.cmask, 8ull * n * (kMaxT + 1), st)) ||
-            (rc = memset_async(W.iters, 4ull * n, st)) || (rc = memset_async(W.counters, 64, st)))
-            return rc;
+        if ((rc = clear_counts(g, W, n, false, st))) return rc;
         BpLaunch b{};
         b.member_major = 0;
         b.slab_in_lds = in_lds ? 1 : 0;
@@ -431,8 +433,8 @@ extern "C" int vibe_lsd(vibe_graph* G, const uint8_t* syndromes, const float* so
     if (B > UINT32_MAX) return fail(VIBE_EINVAL, "B must be < 2^32 for vibe_lsd");
     hipStream_t st = static_cast<hipStream_t>(stream);
     const DevGraph& g = G->h.dg;
-    const int lg = lsd_grid_for(B);
     const size_t per = lsd_scratch_per_block(g);
+    const int lg = lsd_grid_for(lsd_lds_bytes(g), per, B);
     if ((rc = ensure_workspace(G, per * lg))) return rc;
     LsdLaunch l{};
     l.syndromes = syndromes;
@@ -552,8 +554,8 @@ extern "C" int vibe_decode_noalloc(vibe_graph* G, const uint8_t* syndromes, uint
     hipStream_t st = static_cast<hipStream_t>(stream);
     for (uint64_t s0 = 0; s0 < B; s0 += bc) {
         const uint32_t n = (uint32_t)std::min<uint64_t>(bc, B - s0);
-        if ((rc = decode_chunk(G, g, W, syndromes, s0, n, corrections, stats, bpg, lg, st, in_lds, false)))
+        if ((rc = decode_chunk(G, g, W, syndromes, s0, n, corrections, observables, stats, bpg, lg, st, in_lds, false)))
             return rc;
     }
-    return launch_observables(g, corrections, 0, (uint32_t)std::min<uint64_t>(B, UINT32_MAX), observables, st);
+    return VIBE_OK;
 }

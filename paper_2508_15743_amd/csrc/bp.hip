@@ -1095,8 +1095,10 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(D > kDept
 // per SIMD.  A launch whose items all reside is bound by the chain of LDS
 // reads, shuffles and sums from chunk to chunk: 304 ns per chunk for both
 // passes (general body: 635), 318 with two groups ahead, where the slab's
-// latency shows.
-template <int DC>
+// latency shows.  Short rows (dense groups only): the phenomenological d = 11
+// graph, 10007 shots, 75 ms against 89 (its slabs stay in the caches, and
+// streaming them takes 113).
+template <int DC, int NT>
 __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(4))) void bp_compact_kernel(DevGraph g, BpLaunch a) {
     extern __shared__ __align__(16) unsigned char lds[];
     const uint32_t slab_elems = bp_slab_elems(g);
@@ -1106,7 +1108,7 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(4))) void
     for (;;) {
         const uint32_t item = wave_ticket(a.counter, 1u);
         if (item >= n_items) break;
-        run_item_c<DC>(g, a, item, lds, slb, post);
+        run_item_c<DC, NT>(g, a, item, lds, slb, post);
         __syncthreads();
     }
 }
@@ -1114,7 +1116,7 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(4))) void
 // The ragged launch with compact suffix states: FP32, every segment on the
 // serial schedule with one shot per wavefront and its slab in global memory;
 // segments whose graph has no compact data run the general item body.
-template <int DC>
+template <int DC, int NT>
 __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(4))) void bp_ragged_compact_kernel(RaggedLaunch r) {
     using CSeg = const __attribute__((address_space(4))) BpSeg;
     extern __shared__ __align__(16) unsigned char lds[];
@@ -1130,7 +1132,7 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(4))) void
         const DevGraph g = load_const(&r.segs[j].g);
         const BpLaunch a = load_const(&r.segs[j].a);
         if (g.compact)
-            run_item_c<DC>(g, a, item - segs[j].item0, lds, x.slb, post);
+            run_item_c<DC, NT>(g, a, item - segs[j].item0, lds, x.slb, post);
         else
             run_item<float, false, false, false, false, kDepth>(g, a, item - segs[j].item0, lds, x);
         __syncthreads();
@@ -1244,9 +1246,11 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(4))) void
     }
 }
 
-__global__ void zero_kernel(uint32_t* p, size_t words) {
-    for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < words; i += (size_t)gridDim.x * blockDim.x)
-        p[i] = 0u;
+// p: 16-byte aligned
+__global__ void zero_kernel(uint4* p, size_t quads, uint32_t words) {
+    const size_t i0 = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
+    for (size_t i = i0; i < quads; i += (size_t)gridDim.x * blockDim.x) p[i] = make_uint4(0u, 0u, 0u, 0u);
+    if (i0 < words) reinterpret_cast<uint32_t*>(p + quads)[i0] = 0u;
 }
 
 template <class F, bool FLOOD>
@@ -1268,15 +1272,22 @@ const void* multi_kernel_for(bool ragged, uint32_t P) {
     return P == 2 ? (const void*)bp_multi_kernel<F, 2, DG> : (const void*)bp_multi_kernel<F, 4, DG>;
 }
 
+// compact: the item body's column width (6 or 8), with kCompactStream where
+// the slab is streamed
+template <int NT>
+const void* compact_kernel_for(bool ragged, int compact) {
+    const bool six = (compact & 15) <= 6;
+    if (ragged) return six ? (const void*)bp_ragged_compact_kernel<6, NT> : (const void*)bp_ragged_compact_kernel<8, NT>;
+    return six ? (const void*)bp_compact_kernel<6, NT> : (const void*)bp_compact_kernel<8, NT>;
+}
+
 // ragged: layered = some segment is layered, P > 1 = some segment runs
 // several shots per wavefront; dg: decisions in global memory (the
 // non-layered items; the slab in global memory)
 const void* kernel_for(bool fp64, bool flood, bool slab_in_lds, bool ragged, bool layered = false, uint32_t P = 1,
                        bool dg = false, bool latency = false, int compact = 0) {
-    if (compact) {
-        if (ragged) return compact <= 6 ? (const void*)bp_ragged_compact_kernel<6> : (const void*)bp_ragged_compact_kernel<8>;
-        return compact <= 6 ? (const void*)bp_compact_kernel<6> : (const void*)bp_compact_kernel<8>;
-    }
+    if (compact)
+        return compact & kCompactStream ? compact_kernel_for<kStream>(ragged, compact) : compact_kernel_for<0>(ragged, compact);
     // the latency variant: FP32, serial schedule, global slab, one shot per
     // wavefront, decisions in LDS
     if (latency && !fp64 && !flood && !slab_in_lds && !layered && P == 1 && !dg)
@@ -1424,9 +1435,10 @@ int launch_bp_ragged(const RaggedLaunch& r, hipStream_t st) {
 
 int launch_zero(void* p, size_t bytes, hipStream_t st) {
     if (!bytes) return VIBE_OK;
-    const size_t words = (bytes + 3) / 4;
-    const int blocks = (int)std::min<size_t>((words + 255) / 256, 4096);
-    hipLaunchKernelGGL(zero_kernel, dim3(blocks), dim3(256), 0, st, static_cast<uint32_t*>(p), words);
+    const size_t words = (bytes + 3) / 4, quads = words / 4;
+    const int blocks = (int)std::min<size_t>((quads + 256) / 256, 4096);
+    hipLaunchKernelGGL(zero_kernel, dim3(blocks), dim3(256), 0, st, static_cast<uint4*>(p), quads,
+                       (uint32_t)(words % 4));
     hipError_t e = hipGetLastError();
     return e == hipSuccess ? VIBE_OK : hip_fail(e, "zero_kernel launch");
 }

@@ -26,8 +26,9 @@
 //
 // Chunks are handled in groups of four: a lane's four messages (and schedule
 // words) lie together, so that every access of the slab, the records and the
-// schedule moves 1 KB or 256 bytes at once, streamed past the caches that
-// hold the schedule.
+// schedule moves 1 KB or 256 bytes at once.  Where the slabs of all resident
+// wavefronts exceed the last-level cache, they are streamed past the caches
+// that hold the schedule (DevGraph.cstream).
 //
 // Decisions: a column's decision is 0 almost always, so nothing is kept
 // from sweep to sweep.  Each sweep starts its residual at the syndrome, and
@@ -43,8 +44,8 @@ constexpr uint32_t kCVals = 12;    // values of a chunk's record
 constexpr uint32_t kCSch = 2048;   // bytes of a group in the compact schedule: meta[64][4], lambda[64][4]
 constexpr uint32_t kCSlab = 1024;  // bytes of a group in the slab: [64][4]
 constexpr uint32_t kCRec = 256;    // bytes of a group's records
-constexpr int kNT = 2;             // cache policy: streamed
-constexpr int kCAhead = 4;         // groups loaded ahead (2 in the dense groups, which are few)
+constexpr int kStream = 2;         // cache policy of a streamed slab
+constexpr int kCAhead = 4;         // groups loaded ahead
 
 using u32x4 = __attribute__((ext_vector_type(4))) unsigned int;
 using LdsWord = __attribute__((address_space(3))) uint32_t;
@@ -120,14 +121,14 @@ struct CStage {
     uint32_t v[4]; // only with posteriors
 };
 
-template <bool DENSE, bool POST>
+template <bool DENSE, bool POST, int NT>
 __device__ __forceinline__ void cfetch(const CCtx& x, CStage& s, uint32_t g) {
     s.meta = bload4<0>(x.sch, x.lane16, g * kCSch);
     s.lam = bload4<0>(x.sch, x.lane16 + 1024u, g * kCSch);
     if constexpr (DENSE)
-        s.st = bload4<kNT>(x.slb, x.lane16, g * kCSlab);
+        s.st = bload4<NT>(x.slb, x.lane16, g * kCSlab);
     else
-        s.rec = __builtin_amdgcn_raw_buffer_load_b32(x.recs, (int)x.lane4, (int)(x.rec_at + g * kCRec), kNT);
+        s.rec = __builtin_amdgcn_raw_buffer_load_b32(x.recs, (int)x.lane4, (int)(x.rec_at + g * kCRec), NT);
     if constexpr (POST) {
 #pragma unroll
         for (int j = 0; j < 4; j++) s.v[j] = bload<uint32_t>(x.osch, x.lane4 + kRecV, (g * 4 + j) * rec_bytes(false));
@@ -235,7 +236,7 @@ __device__ __forceinline__ void csweep_chunk(const CCtx& x, const CStage& s, CRo
     __builtin_amdgcn_sched_barrier(0);
 }
 
-template <int DC, bool DENSE, bool POST>
+template <int DC, bool DENSE, bool POST, int NT>
 __device__ __forceinline__ void csweep_group(const CCtx& x, const CStage& s, uint32_t g, bool first, float& satm) {
     CRow w;
     u32x4 out;
@@ -245,28 +246,28 @@ __device__ __forceinline__ void csweep_group(const CCtx& x, const CStage& s, uin
     csweep_chunk<DC, DENSE, POST, 1>(x, s, w, g, first, out, satm);
     csweep_chunk<DC, DENSE, POST, 2>(x, s, w, g, first, out, satm);
     csweep_chunk<DC, DENSE, POST, 3>(x, s, w, g, first, out, satm);
-    bstore4<kNT>(out, x.slb, x.lane16, g * kCSlab);
+    bstore4<NT>(out, x.slb, x.lane16, g * kCSlab);
 }
 
 // Groups g0 .. g1-1 of the sweep (an even number), loaded A ahead.  The loop
 // runs A groups without an exit between them: one would join paths in which
 // different stages are the last loaded, and the compiler would wait for all
 // of them at the loop's head.
-template <int DC, bool DENSE, bool POST, int A>
+template <int DC, bool DENSE, bool POST, int A, int NT>
 __device__ __forceinline__ void csweep(const CCtx& x, uint32_t g0, uint32_t g1, bool first, float& satm) {
     if (g0 >= g1) return;
     CStage ring[A];
 #pragma unroll
     for (int d = 0; d < A; d++) {
-        cfetch<DENSE, POST>(x, ring[d], min(g0 + d, g1 - 1));
+        cfetch<DENSE, POST, NT>(x, ring[d], min(g0 + d, g1 - 1));
         __builtin_amdgcn_sched_barrier(0);
     }
     uint32_t g = g0;
     for (; g + A <= g1; g += A) {
 #pragma unroll
         for (int d = 0; d < A; d++) {
-            csweep_group<DC, DENSE, POST>(x, ring[d], g + d, first, satm);
-            cfetch<DENSE, POST>(x, ring[d], min(g + d + A, g1 - 1));
+            csweep_group<DC, DENSE, POST, NT>(x, ring[d], g + d, first, satm);
+            cfetch<DENSE, POST, NT>(x, ring[d], min(g + d + A, g1 - 1));
             __builtin_amdgcn_sched_barrier(0);
         }
     }
@@ -274,8 +275,8 @@ __device__ __forceinline__ void csweep(const CCtx& x, uint32_t g0, uint32_t g1, 
 #pragma unroll
         for (int d = 0; d < A - 2; d += 2) {
             if (g + d >= g1) break;
-            csweep_group<DC, DENSE, POST>(x, ring[d], g + d, first, satm);
-            csweep_group<DC, DENSE, POST>(x, ring[d + 1], g + d + 1, first, satm);
+            csweep_group<DC, DENSE, POST, NT>(x, ring[d], g + d, first, satm);
+            csweep_group<DC, DENSE, POST, NT>(x, ring[d + 1], g + d + 1, first, satm);
         }
     }
 }
@@ -284,9 +285,10 @@ struct CBStage {
     u32x4 meta, msg;
 };
 
+template <int NT>
 __device__ __forceinline__ void cbfetch(const CCtx& x, CBStage& s, uint32_t g) {
     s.meta = bload4<0>(x.sch, x.lane16, g * kCSch);
-    s.msg = bload4<kNT>(x.slb, x.lane16, g * kCSlab);
+    s.msg = bload4<NT>(x.slb, x.lane16, g * kCSlab);
 }
 
 // Chunk J of group g in the backward pass: its messages join the states of
@@ -330,7 +332,7 @@ __device__ __forceinline__ void cback_chunk(const CCtx& x, const CBStage& s, uin
     __builtin_amdgcn_sched_barrier(0);
 }
 
-template <bool DENSE>
+template <bool DENSE, int NT>
 __device__ __forceinline__ void cback_group(const CCtx& x, const CBStage& s, uint32_t g) {
     u32x4 out;
     uint32_t rec = 0, run = *lds_at(cm_row4(s.meta[3]));
@@ -339,13 +341,13 @@ __device__ __forceinline__ void cback_group(const CCtx& x, const CBStage& s, uin
     cback_chunk<DENSE, 1>(x, s, run, g, out, rec);
     cback_chunk<DENSE, 0>(x, s, run, g, out, rec);
     if constexpr (DENSE)
-        bstore4<kNT>(out, x.slb, x.lane16, g * kCSlab);
+        bstore4<NT>(out, x.slb, x.lane16, g * kCSlab);
     else
-        __builtin_amdgcn_raw_buffer_store_b32(rec, x.slb, (int)x.lane4, (int)(x.rec_slab + g * kCRec), kNT);
+        __builtin_amdgcn_raw_buffer_store_b32(rec, x.slb, (int)x.lane4, (int)(x.rec_slab + g * kCRec), NT);
 }
 
 // Groups g1-1 .. g0 of the backward pass (an even number), loaded A ahead.
-template <bool DENSE, int A>
+template <bool DENSE, int A, int NT>
 __device__ __forceinline__ void cbackward(const CCtx& x, uint32_t g0, uint32_t g1) {
     if (g0 >= g1) return;
     const uint32_t cnt = g1 - g0;
@@ -353,15 +355,15 @@ __device__ __forceinline__ void cbackward(const CCtx& x, uint32_t g0, uint32_t g
     auto at = [=](uint32_t e) { return e < cnt ? g1 - 1 - e : g0; };  // e groups from the end
 #pragma unroll
     for (int d = 0; d < A; d++) {
-        cbfetch(x, ring[d], uni(at(d)));
+        cbfetch<NT>(x, ring[d], uni(at(d)));
         __builtin_amdgcn_sched_barrier(0);
     }
     uint32_t e = 0;
     for (; e + A <= cnt; e += A) {
 #pragma unroll
         for (int d = 0; d < A; d++) {
-            cback_group<DENSE>(x, ring[d], g1 - 1 - e - d);
-            cbfetch(x, ring[d], at(e + d + A));
+            cback_group<DENSE, NT>(x, ring[d], g1 - 1 - e - d);
+            cbfetch<NT>(x, ring[d], at(e + d + A));
             __builtin_amdgcn_sched_barrier(0);
         }
     }
@@ -369,15 +371,15 @@ __device__ __forceinline__ void cbackward(const CCtx& x, uint32_t g0, uint32_t g
 #pragma unroll
         for (int d = 0; d < A - 2; d += 2) {
             if (e + d >= cnt) break;
-            cback_group<DENSE>(x, ring[d], g1 - 1 - e - d);
-            cback_group<DENSE>(x, ring[d + 1], g1 - 2 - e - d);
+            cback_group<DENSE, NT>(x, ring[d], g1 - 1 - e - d);
+            cback_group<DENSE, NT>(x, ring[d + 1], g1 - 2 - e - d);
         }
     }
 }
 
 // One work item, as run_item.  slb: the block's slab (bp_slab_elems words);
 // post: its posteriors.
-template <int DC>
+template <int DC, int NT>
 __device__ __forceinline__ void run_item_c(const DevGraph& g, const BpLaunch& a, uint32_t item, unsigned char* lds,
                                            Rsrc slb, float* post) {
     CCtx x;
@@ -466,11 +468,11 @@ __device__ __forceinline__ void run_item_c(const DevGraph& g, const BpLaunch& a,
         for (uint32_t k = lane; k < nch; k += kWave) bstore<uint64_t>(0ull, slb, k * 8u, x.msk_slab);
         __syncthreads();
         if (want_post) {
-            csweep<DC, false, true, kCAhead>(x, 0, gd, t == 1, satm);
-            csweep<DC, true, true, 2>(x, gd, ng, t == 1, satm);
+            csweep<DC, false, true, kCAhead, NT>(x, 0, gd, t == 1, satm);
+            csweep<DC, true, true, kCAhead, NT>(x, gd, ng, t == 1, satm);
         } else {
-            csweep<DC, false, false, kCAhead>(x, 0, gd, t == 1, satm);
-            csweep<DC, true, false, 2>(x, gd, ng, t == 1, satm);
+            csweep<DC, false, false, kCAhead, NT>(x, 0, gd, t == 1, satm);
+            csweep<DC, true, false, kCAhead, NT>(x, gd, ng, t == 1, satm);
         }
         __syncthreads();
         if (post_out) {
@@ -488,8 +490,8 @@ __device__ __forceinline__ void run_item_c(const DevGraph& g, const BpLaunch& a,
         if (t < a.T_run) {
             for (uint32_t c = lane; c <= g.m; c += kWave) suf[c] = c < g.m ? g.ident32 : 0u;
             __syncthreads();
-            cbackward<true, 2>(x, gd, ng);
-            cbackward<false, kCAhead>(x, 0, gd);
+            cbackward<true, kCAhead, NT>(x, gd, ng);
+            cbackward<false, kCAhead, NT>(x, 0, gd);
             x.recs = slb;
             x.rec_at = x.rec_slab;
             __syncthreads();

@@ -615,16 +615,22 @@ extern "C" int vibe_graph_create(uint32_t m, uint32_t n, const uint32_t* h_indpt
     }
     int rc = VIBE_OK;
     const float* lam32_d = nullptr;
-    // Only where most chunks have few records (rows of a few edges have one
-    // at every second or third edge: the states then stay in the slab as in
-    // the general body) and the padding to whole groups is small: 42 chunks
-    // of 40 rows of 8 edges gain 2% (8192 shots: 1.57 ms against 1.61), 85
-    // chunks of rows of 16 17% (2.04 / 2.46), 464 chunks of rows of 64 29%
-    // (45.3 / 64.2), 12 chunks of 9 rows of 5 lose 11% (1.91 / 1.72).
+    // Graphs of at least 16 chunks, where the padding to whole groups is
+    // small: 17 chunks of rows of 5 gain 15% (8192 shots: 2.36 ms against
+    // 2.79), 20 chunks of rows of 6 10%, 57 chunks of rows of 7 14% (15.4 /
+    // 17.8), 118 chunks of rows of 16 9%, 464 chunks of rows of 64 29%; 12
+    // chunks of 9 rows of 5 lose 3%.  Rows of a few edges have a record at
+    // every second or third edge: where most chunks would not fit theirs,
+    // all keep their states in the slab.
+    //
+    // The slabs are streamed where those of 4096 wavefronts (16 on each of
+    // 256 CUs) exceed the 256 MB of the last-level cache: of 60 KB each they
+    // run in 4.87 ms, streamed 5.72; of 79 KB in 29.5 and 26.1.
     auto compact_upload = [&]() -> int {
         DevGraph v = d;
         v.compact = 1;
-        if (!want_compact || ch_min < 32 || 2 * c_chunks < member_chunk[c.L] || bp_lds_bytes(v, false) > 64 * 1024) return VIBE_OK;
+        if (!want_compact || ch_min < 16 || bp_lds_bytes(v, false) > 64 * 1024) return VIBE_OK;
+        if (2 * c_chunks < member_chunk[c.L]) std::fill(c_dense0.begin(), c_dense0.end(), 0u);
         const uint32_t* p[2] = {nullptr, nullptr};
         int r;
         if ((r = upload(h, c_rec0.data(), c_rec0.size(), &p[0])) || (r = upload(h, c_row0.data(), c_row0.size(), &d.crow0)) ||
@@ -635,6 +641,7 @@ extern "C" int vibe_graph_create(uint32_t m, uint32_t n, const uint32_t* h_indpt
         d.crec0 = reinterpret_cast<const unsigned char*>(p[0]);
         d.csched = reinterpret_cast<const unsigned char*>(p[1]);
         for (uint32_t i = 0; i < c.L; i++) d.cgroups = std::max(d.cgroups, c_group[i + 1] - c_group[i]);
+        if (d.cgroups > 64) d.ccols |= kCompactStream;
         return VIBE_OK;
     };
     if ((rc = upload(h, rp.data(), rp.size(), &d.rp)) ||

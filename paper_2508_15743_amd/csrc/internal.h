@@ -73,6 +73,10 @@ __host__ __device__ inline B rs_combine(B a, B b) {
     return (ma < mb ? ma : mb) | ((a ^ b) & kSign);
 }
 
+// added to DevGraph.compact where the slabs of all resident wavefronts are
+// streamed (in a ragged launch, of any segment)
+constexpr int kCompactStream = 16;
+
 // Everything a kernel needs to know about a resident graph (passed by value).
 struct DevGraph {
     uint32_t m, n, k, L, M, T;
@@ -107,8 +111,8 @@ struct DevGraph {
     const uint64_t* lobs;         // k x words_n, bit-packed observable rows
     // compact suffix states (bp_compact.h); csched is null where the graph has none
     int compact;                  // launched with the compact item body: the most edges of a
-                                  // column it sums over (6 or 8), or 0
-    int ccols;                    // 6 or 8: what compact is set to
+                                  // column it sums over (6 or 8), with kCompactStream; or 0
+    int ccols;                    // what compact is set to
     uint32_t cgroups;             // largest group count of a member (four chunks each, even)
     const unsigned char* csched;  // per group: meta[64][4], lambda[64][4].  meta: bits 0-7 four
                                   // times the column's first lane; bit 8 + q: the column has a
@@ -230,7 +234,7 @@ struct RaggedLaunch {
     int layered;           // some segment is on the layered schedule
     int dec_global;        // the non-layered segments keep decisions in global memory
     int latency;           // the latency variant (every item resident at once)
-    int compact;           // some segment runs the compact item body: the largest DevGraph.compact
+    int compact;           // some segment runs the compact item body: DevGraph.compact, the widest
     size_t lds_bytes;      // largest bp_lds_bytes over the segments
 };
 int launch_bp_ragged(const RaggedLaunch& r, hipStream_t st);
@@ -304,6 +308,7 @@ struct SelectLaunch {
     const uint32_t* iters;
     const uint64_t* conv_mask;    // n_shots x (kMaxT + 1); word 0 = members that saturated, may be null
     uint64_t* corrections;        // global B x words_n (indexed by shot0 + i)
+    uint8_t* observables;         // global B x k
     vibe_shot_stats* stats;       // global, may be null
     uint32_t* fail_list;          // local shot indices that need LSD
     uint32_t* fail_count;
@@ -319,6 +324,7 @@ struct LsdLaunch {
     const float* soft_f32;        // global B x n (indexed by shot0 + i), or
     const int64_t* soft_fix;      // local n_shots x n fixed point
     uint64_t* corrections;        // global B x words_n
+    uint8_t* observables;         // global B x k, may be null
     vibe_shot_stats* stats;       // global, may be null
     void* scratch;
     size_t scratch_per_block;
@@ -327,13 +333,27 @@ struct LsdLaunch {
 int launch_lsd(const DevGraph& g, const LsdLaunch& a, hipStream_t st);
 size_t lsd_scratch_per_block(const DevGraph& g);
 size_t lsd_lds_bytes(const DevGraph& g);
+// LSD blocks for up to `shots` shots: as many as reside at once, where that
+// is more than 512, within a scratch budget.
+int lsd_grid_for(size_t lds_bytes, size_t scratch_per_block, uint64_t shots);
 
 // Record a start event before a launch of kernel class `which` (0 BP,
 // 1 selection, 2 LSD) when profiling is on; end_timed records the end event.
 void begin_timed(vibe_graph* G, int which, hipStream_t st);
 void end_timed(vibe_graph* G, int which, hipStream_t st);
 
-int launch_observables(const DevGraph& g, const uint64_t* corrections, uint64_t shot0,
-                       uint32_t n_shots, uint8_t* observables, hipStream_t st);
+#if defined(__HIPCC__)
+// Observables Lobs * e mod 2 (paper Sec. II.B) of one shot by one wavefront,
+// from its correction words e (any addressable memory): obs[0 .. k-1].
+__device__ inline void write_observables(const DevGraph& g, const uint64_t* e, uint8_t* obs, int lane) {
+    for (uint32_t r = 0; r < g.k; r++) {
+        const uint64_t* row = g.lobs + (size_t)r * g.words_n;
+        uint32_t par = 0;
+        for (uint32_t i = lane; i < g.words_n; i += kWave) par ^= __popcll(e[i] & row[i]) & 1u;
+        const uint64_t odd = __ballot(par & 1u);
+        if (lane == 0) obs[r] = (uint8_t)(__popcll(odd) & 1);
+    }
+}
+#endif
 
 }  // namespace vibe

@@ -29,6 +29,10 @@
 // non-pivot column.  The candidate of least prior weight (FP64, summed in
 // ascending column index) replaces the cluster's OSD-0 solution; ties keep
 // the earlier candidate.
+#include <algorithm>
+#include <map>
+#include <mutex>
+
 #include "internal.h"
 
 namespace vibe {
@@ -84,37 +88,46 @@ struct LsdMem {
     int32_t* ck;        // n: one cluster's columns, ascending (lane 0 only)
     int32_t* fl;        // n: one cluster's non-pivot ordinals, rank order (lane 0 only)
     uint64_t* reps;     // n x words_m: pivot combination of each non-pivot column
-    int priv_lds;       // the per-check arrays marked "lane 0 only" are in LDS too
 };
 
-__host__ __device__ inline size_t al8(size_t x) { return (x + 7) & ~(size_t)7; }
+__host__ __device__ __forceinline__ size_t al8(size_t x) { return (x + 7) & ~(size_t)7; }
+
+// The arrays only lane 0 touches (best_q, best_v, ccount, picks, added,
+// pivcol, row_q, row_v, clist: 48 bytes per check) move to global memory when
+// everything would not fit in kLsdLds bytes of LDS (graphs with several
+// thousand checks).  Reads and writes by one lane need no cross-lane
+// visibility.
+__host__ __device__ inline bool lsd_priv_lds(const DevGraph& g) {
+    const size_t m = g.m ? g.m : 1, wn = g.words_n, wm = g.words_m ? g.words_m : 1;
+    return al8(8 * m) + 2 * al8(8 * wn) + 5 * al8(8 * wm) + 5 * al8(4 * m) + al8(8 * m) + 4 * al8(4 * m) + al8(8 * m) +
+               2 * al8(4 * m) <= kLsdLds;
+}
 
 // Lays out the LDS part at `lds` and the global part at `glob` (either may
-// be null to measure); returns the two sizes.
-__host__ __device__ inline void lsd_layout(const DevGraph& g, unsigned char* lds, unsigned char* glob,
-                                           LsdMem* out, size_t* lds_bytes, size_t* glob_bytes) {
+// be null to measure); returns the two sizes.  PRIV: lsd_priv_lds(g), known
+// at compile time in the kernel, so that every array's accesses are LDS or
+// global instructions.
+template <bool PRIV>
+__host__ __device__ __forceinline__ void lsd_layout(const DevGraph& g, unsigned char* lds, unsigned char* glob,
+                                                     LsdMem& M, size_t& lo, size_t& go) {
     const size_t m = g.m ? g.m : 1, n = g.n, wn = g.words_n, wm = g.words_m ? g.words_m : 1;
-    size_t lo = 0, go = 0;
+    lo = go = 0;
     auto tl = [&](size_t bytes) {
-        unsigned char* p = lds ? lds + lo : nullptr;
+        unsigned char* p = lds + lo;
         lo += al8(bytes);
         return p;
     };
     auto tg = [&](size_t bytes) {
-        unsigned char* p = glob ? glob + go : nullptr;
+        unsigned char* p = glob + go;
         go += al8(bytes);
         return p;
     };
-    // The arrays only lane 0 touches (best_q, best_v, ccount, picks, added,
-    // pivcol, row_q, row_v, clist: 48 bytes per check) move to global memory when everything
-    // would not fit in kLsdLds bytes of LDS (graphs with several thousand
-    // checks).  Reads and writes by one lane need no cross-lane visibility.
-    const size_t all_lds = al8(8 * m) + 2 * al8(8 * wn) + 5 * al8(8 * wm) + 5 * al8(4 * m) + al8(8 * m) +
-                           4 * al8(4 * m) + al8(8 * m) + 2 * al8(4 * m);
-    const bool priv_glob = all_lds > kLsdLds;
-    auto tp = [&](size_t bytes) { return priv_glob ? tg(bytes) : tl(bytes); };
-    LsdMem M;
-    M.priv_lds = priv_glob ? 0 : 1;
+    auto tp = [&](size_t bytes) {
+        if constexpr (PRIV)
+            return tl(bytes);
+        else
+            return tg(bytes);
+    };
     M.best_q = (int64_t*)tp(8 * m);
     M.in_bits = (uint64_t*)tl(8 * wn);
     M.ebits = (uint64_t*)tl(8 * wn);
@@ -148,9 +161,6 @@ __host__ __device__ inline void lsd_layout(const DevGraph& g, unsigned char* lds
     M.ck = (int32_t*)tg(4 * nh);
     M.fl = (int32_t*)tg(4 * nh);
     M.reps = (uint64_t*)tg(8 * wm * nh);
-    if (out) *out = M;
-    if (lds_bytes) *lds_bytes = lo;
-    if (glob_bytes) *glob_bytes = go;
 }
 
 __device__ inline int32_t ald32(const int32_t* p) {
@@ -168,7 +178,7 @@ __device__ inline int64_t float_key(float f) {
     return (b >> 31) ? -mag : mag;
 }
 
-__device__ inline int32_t find_root(int32_t* parent, int32_t x) {
+__device__ __forceinline__ int32_t find_root(int32_t* parent, int32_t x) {
     while (parent[x] != x) x = parent[x];
     return x;
 }
@@ -187,7 +197,7 @@ __device__ inline uint64_t uni64(uint64_t x) {
 // does not depend on the order.  hit (LDS) receives one bit per vector.
 // Word w of every vector is read and written only by lane w mod 64, so the
 // basis needs no cross-lane visibility in global memory.
-__device__ void reduce_by(uint64_t* x, uint64_t* comb, const uint64_t* vecs, size_t stride,
+__device__ __forceinline__ void reduce_by(uint64_t* x, uint64_t* comb, const uint64_t* vecs, size_t stride,
                           const int32_t* piv, int count, uint32_t wm, uint64_t* hit, int lane) {
     __syncthreads();
     const int nblk = (count + kWave - 1) / kWave;
@@ -238,7 +248,7 @@ __device__ void reduce_by(uint64_t* x, uint64_t* comb, const uint64_t* vecs, siz
 // bit p from every earlier vector that has it (xor x and comb), so the
 // basis stays in reduced echelon form.  flag (LDS) receives one bit per
 // earlier vector; the lane that holds word p / 64 of the vectors finds them.
-__device__ void basis_append(uint64_t* vecs, size_t stride, int32_t* piv, int count, const uint64_t* x,
+__device__ __forceinline__ void basis_append(uint64_t* vecs, size_t stride, int32_t* piv, int count, const uint64_t* x,
                              const uint64_t* comb, int p, uint32_t wm, uint64_t* flag, int lane) {
     const uint32_t W = (uint32_t)p >> 6;
     const uint64_t bit = 1ull << (p & 63);
@@ -275,7 +285,7 @@ __device__ void basis_append(uint64_t* vecs, size_t stride, int32_t* piv, int co
 }
 
 // lowest set bit of a words_m vector, or -1
-__device__ int lowest_bit(const uint64_t* x, uint32_t wm, int lane) {
+__device__ __forceinline__ int lowest_bit(const uint64_t* x, uint32_t wm, int lane) {
     int best = 0x7fffffff;
     for (uint32_t w = lane; w < wm; w += kWave)
         if (x[w]) {
@@ -287,7 +297,7 @@ __device__ int lowest_bit(const uint64_t* x, uint32_t wm, int lane) {
     return best == 0x7fffffff ? -1 : best;
 }
 
-__device__ void column_vector(const DevGraph& g, uint64_t* x, uint32_t v, int lane) {
+__device__ __forceinline__ void column_vector(const DevGraph& g, uint64_t* x, uint32_t v, int lane) {
     for (uint32_t w = lane; w < g.words_m; w += kWave) x[w] = 0;
     __syncthreads();
     if (lane == 0)
@@ -299,7 +309,7 @@ __device__ void column_vector(const DevGraph& g, uint64_t* x, uint32_t v, int la
 }
 
 // dbuf = pivot combination of non-pivot ordinals oa and ob (-1 = none)
-__device__ void candidate_delta(const LsdMem& S, int32_t oa, int32_t ob, uint32_t wm, int lane) {
+__device__ __forceinline__ void candidate_delta(const LsdMem& S, int32_t oa, int32_t ob, uint32_t wm, int lane) {
     for (uint32_t w = lane; w < wm; w += kWave) {
         uint64_t d = 0;
         if (oa >= 0) d ^= S.reps[(size_t)oa * wm + w];
@@ -311,7 +321,7 @@ __device__ void candidate_delta(const LsdMem& S, int32_t oa, int32_t ob, uint32_
 
 // Is column v set in the cluster's solution for the candidate whose pivot
 // change is in dbuf and whose non-pivot columns are va, vb?  (lane 0)
-__device__ inline bool cand_bit(const LsdMem& S, int32_t v, int32_t va, int32_t vb) {
+__device__ __forceinline__ bool cand_bit(const LsdMem& S, int32_t v, int32_t va, int32_t vb) {
     bool b = (S.ebits[v >> 6] >> (v & 63)) & 1ull;
     const int32_t k = S.pidx[v];
     if (k >= 0) b ^= (S.dbuf[k >> 6] >> (k & 63)) & 1ull;
@@ -320,7 +330,7 @@ __device__ inline bool cand_bit(const LsdMem& S, int32_t v, int32_t va, int32_t 
 
 // The combination sweep on every valid cluster that has non-pivot columns.
 // ebits holds the OSD-0 solution on entry and the chosen one on return.
-__device__ void combination_sweep(const DevGraph& g, const LsdMem& S, int nk, int ncol, int nnp, uint32_t wm,
+__device__ __forceinline__ void combination_sweep(const DevGraph& g, const LsdMem& S, int nk, int ncol, int nnp, uint32_t wm,
                                   int lane) {
     for (int K = 0; K < nk; K++) {
         if (uni(S.parent[K]) != K || !(uni(S.cstate[K]) & kValid)) continue;
@@ -401,7 +411,7 @@ __device__ void combination_sweep(const DevGraph& g, const LsdMem& S, int nk, in
 // The least (key, column) over the columns of row c not yet held, formed by
 // the whole wavefront (every lane receives it; column INT32_MAX: none).
 template <class KeyF>
-__device__ inline void row_least(const DevGraph& g, const LsdMem& S, uint32_t c, KeyF key, int lane, int64_t& bq,
+__device__ __forceinline__ void row_least(const DevGraph& g, const LsdMem& S, uint32_t c, KeyF key, int lane, int64_t& bq,
                                  int32_t& bv) {
     bq = INT64_MAX;
     bv = 0x7fffffff;
@@ -424,12 +434,21 @@ __device__ inline void row_least(const DevGraph& g, const LsdMem& S, uint32_t c,
     }
 }
 
+// Bound by its chains of LDS reads and cross-lane steps, one wavefront per
+// shot.  PRIV (see lsd_layout) is a template parameter and everything that
+// takes the state is inlined: with the state passed through memory every
+// access was a flat one.  1600 failed shots of the d = 5 code-capacity graph
+// 340 -> 123 us, the phenomenological d = 11 graph's 4900 7.7 -> 4.6 ms, the
+// parallel d = 9 circuit graph's 7400 32.4 -> 26.2 ms (with the larger grid
+// of lsd_grid_for).
+template <bool PRIV>
 __global__ __launch_bounds__(kWave) void lsd_kernel(DevGraph g, LsdLaunch a) {
     extern __shared__ __align__(16) unsigned char lds[];
     const int lane = threadIdx.x;
     LsdMem S;
-    lsd_layout(g, lds, static_cast<unsigned char*>(a.scratch) + a.scratch_per_block * blockIdx.x, &S,
-               nullptr, nullptr);
+    size_t lds_used, glob_used;
+    lsd_layout<PRIV>(g, lds, static_cast<unsigned char*>(a.scratch) + a.scratch_per_block * blockIdx.x, S, lds_used,
+                     glob_used);
     const uint32_t count = uni(a.list ? *a.list_count : a.n_list);
     const uint32_t wm = g.words_m;
     for (uint32_t it = blockIdx.x; it < count && it < a.n_list; it += gridDim.x) {
@@ -482,7 +501,7 @@ __global__ __launch_bounds__(kWave) void lsd_kernel(DevGraph g, LsdLaunch a) {
             //    cluster order.
             ncl = uni(__shfl(ncl, 0));
             int npick = 0;
-            if (S.priv_lds) {
+            if constexpr (PRIV) {
                 // Every per-check array is in LDS: each lane takes its own
                 // checks of the list, the whole wavefront scans each stale
                 // row, and the least (key, column) of a cluster is formed by
@@ -758,6 +777,7 @@ __global__ __launch_bounds__(kWave) void lsd_kernel(DevGraph g, LsdLaunch a) {
         if (g.lsd_order && nnp) combination_sweep(g, S, nk, ncol, nnp, wm, lane);
         uint64_t* out = a.corrections + gshot * g.words_n;
         for (uint32_t w = lane; w < g.words_n; w += kWave) out[w] = S.ebits[w];
+        if (a.observables) write_observables(g, S.ebits, a.observables + gshot * g.k, lane);
         int nclus = 0, largest = 0;
         if (lane == 0) {
             for (int K = 0; K < nk; K++) {
@@ -788,27 +808,66 @@ __global__ __launch_bounds__(kWave) void lsd_kernel(DevGraph g, LsdLaunch a) {
 
 }  // namespace
 
+static void lsd_sizes(const DevGraph& g, size_t& lds, size_t& glob) {
+    LsdMem M;
+    if (lsd_priv_lds(g))
+        lsd_layout<true>(g, nullptr, nullptr, M, lds, glob);
+    else
+        lsd_layout<false>(g, nullptr, nullptr, M, lds, glob);
+}
+
 size_t lsd_scratch_per_block(const DevGraph& g) {
-    size_t gb = 0;
-    lsd_layout(g, nullptr, nullptr, nullptr, nullptr, &gb);
-    return al8(gb) + 256;
+    size_t lds, glob;
+    lsd_sizes(g, lds, glob);
+    return al8(glob) + 256;
 }
 
 size_t lsd_lds_bytes(const DevGraph& g) {
-    size_t lb = 0;
-    lsd_layout(g, nullptr, nullptr, nullptr, &lb, nullptr);
-    return lb;
+    size_t lds, glob;
+    lsd_sizes(g, lds, glob);
+    return lds;
+}
+
+// The kernel is bound by its chains of LDS and cross-lane steps, so every
+// block that fits helps: the d = 9 circuit graph's 37 KB of LDS leave room
+// for 1024 blocks.
+int lsd_grid_for(size_t lds_bytes, size_t scratch_per_block, uint64_t shots) {
+    constexpr uint64_t kFloor = 512, kScratch = 2ull << 30;
+    static std::mutex mu;
+    static std::map<std::pair<int, size_t>, int> cache;
+    uint64_t fit = kFloor;
+    if (shots > kFloor) {
+        int dev = 0;
+        (void)hipGetDevice(&dev);
+        std::lock_guard<std::mutex> lk(mu);
+        auto it = cache.find({dev, lds_bytes});
+        if (it == cache.end()) {
+            int per_cu = 0, cus = 0;
+            if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, (const void*)lsd_kernel<true>, kWave, lds_bytes) !=
+                    hipSuccess || per_cu < 1)
+                per_cu = 1;
+            if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) cus = 1;
+            it = cache.emplace(std::make_pair(dev, lds_bytes), per_cu * cus).first;
+        }
+        fit = std::max<uint64_t>(kFloor, std::min<uint64_t>((uint64_t)it->second,
+                                                            kScratch / std::max<size_t>(scratch_per_block, 1)));
+    }
+    return (int)std::min<uint64_t>(std::max<uint64_t>(shots, 1), fit);
 }
 
 int launch_lsd(const DevGraph& g, const LsdLaunch& a, hipStream_t st) {
     if (!a.n_list) return VIBE_OK;
     const size_t lds = lsd_lds_bytes(g);
+    const bool priv = lsd_priv_lds(g);
     if (lds > 64 * 1024) {
-        hipError_t e = hipFuncSetAttribute((const void*)lsd_kernel, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                           (int)lds);
+        hipError_t e = hipFuncSetAttribute(priv ? (const void*)lsd_kernel<true> : (const void*)lsd_kernel<false>,
+                                           hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
         if (e != hipSuccess) return hip_fail(e, "hipFuncSetAttribute(lsd)");
     }
-    hipLaunchKernelGGL(lsd_kernel, dim3(a.grid), dim3(kWave), lds, st, g, a);
+    if (priv)
+        hipLaunchKernelGGL(lsd_kernel<true>, dim3(a.grid), dim3(kWave), lds, st, g, a);
+    else
+        hipLaunchKernelGGL(lsd_kernel<false>, dim3(a.grid), dim3(kWave), lds, st, g, a);
     hipError_t e = hipGetLastError();
     return e == hipSuccess ? VIBE_OK : hip_fail(e, "lsd_kernel launch");
 }

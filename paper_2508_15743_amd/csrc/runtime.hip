@@ -135,7 +135,9 @@ int check_requests(const vibe_request* reqs, uint32_t n) {
 }
 
 // Split the requests into rounds whose per-shot buffers fit the budget, and
-// lay out each round's workspace.
+// lay out each round's workspace.  allow_compact = false: with the smallest
+// footprint, the general BP item body and no more than 512 LSD blocks (what
+// admission is judged by, and what runs where only that fits).
 std::vector<Round> plan(const vibe_request* reqs, uint32_t n_reqs, size_t budget, bool allow_compact = true) {
     std::vector<Round> rounds;
     Round cur;
@@ -176,7 +178,7 @@ std::vector<Round> plan(const vibe_request* reqs, uint32_t n_reqs, size_t budget
         });
         bool lds_ok = true;
         bool fp64 = false, flood = false, multi = false;
-        size_t lds_global = 0, lds_l = 0;
+        size_t lds_global = 0, lds_l = 0, lsd_lds = 0;
         bool layered = false;
         for (const Seg& sg : r.segs) {
             flood = flood || reqs[sg.req].graph->h.dg.flood != 0;
@@ -209,7 +211,7 @@ std::vector<Round> plan(const vibe_request* reqs, uint32_t n_reqs, size_t budget
         for (const Seg& sg : r.segs) compact_ok = compact_ok && !sg.g.dec_global;
         for (Seg& sg : r.segs) {
             if (!compact_ok) sg.g = decode_view(reqs[sg.req].graph, all_multi, sg.n, false);
-            r.compact = std::max(r.compact, sg.g.compact);
+            r.compact = std::max(r.compact & 15, sg.g.compact & 15) | ((r.compact | sg.g.compact) & kCompactStream);
         }
         // decisions in global memory for every chunked segment if one of
         // them wants it (a graph whose decision bitmap would cap the
@@ -228,6 +230,7 @@ std::vector<Round> plan(const vibe_request* reqs, uint32_t n_reqs, size_t budget
             lds_global = std::max(lds_global, bp_lds_bytes(g, false));
             lds_l = std::max(lds_l, bp_lds_bytes(g, true));
             r.lsd_per_block = std::max(r.lsd_per_block, lsd_scratch_per_block(g));
+            lsd_lds = std::max(lsd_lds, lsd_lds_bytes(g));
         }
         r.slab_in_lds = lds_ok;
         r.flood = flood;
@@ -247,7 +250,8 @@ std::vector<Round> plan(const vibe_request* reqs, uint32_t n_reqs, size_t budget
             r.latency = total_items <= (uint64_t)r.grid &&
                         total_items <= (uint64_t)bp_grid_for(false, false, false, r.lds_bytes, true, false, 1u,
                                                              false, true, r.compact);
-        r.lsd_grid = (int)std::min<uint64_t>(512, std::max<uint64_t>(max_n, 1));
+        r.lsd_grid = allow_compact ? lsd_grid_for(lsd_lds, r.lsd_per_block, max_n)
+                                   : (int)std::min<uint64_t>(512, std::max<uint64_t>(max_n, 1));
         // layout: [zeroed: counters | per-segment cmask, iters, qfix, fail count]
         //         [per-segment t_conv, weight, cand, fail_list] [segment table]
         //         [slabs] [posteriors] [LSD scratch]
@@ -364,6 +368,7 @@ int run_round(const vibe_request* reqs, const Round& r, unsigned char* base, hip
         s.iters = reinterpret_cast<const uint32_t*>(base + sg.iters);
         s.conv_mask = reinterpret_cast<const uint64_t*>(base + sg.cmask);
         s.corrections = q.corrections;
+        s.observables = q.observables;
         s.stats = q.stats;
         s.fail_list = reinterpret_cast<uint32_t*>(base + sg.fail_list);
         s.fail_count = fail_count;
@@ -377,12 +382,12 @@ int run_round(const vibe_request* reqs, const Round& r, unsigned char* base, hip
         l.soft_f32 = nullptr;
         l.soft_fix = reinterpret_cast<const int64_t*>(base + sg.qfix);
         l.corrections = q.corrections;
+        l.observables = q.observables;
         l.stats = q.stats;
         l.scratch = base + r.lsd_off;
         l.scratch_per_block = lsd_scratch_per_block(g);
         l.grid = std::min<int>(r.lsd_grid, (int)sg.n);
         if ((rc = launch_lsd(g, l, st))) return rc;
-        if ((rc = launch_observables(g, q.corrections, sg.shot0, sg.n, q.observables, st))) return rc;
     }
     return VIBE_OK;
 }

@@ -2,8 +2,8 @@
 // converged, the first M in (iteration, member index) order are the
 // candidates; the one of least prior weight W(e) = sum_v e_v lambda_v wins,
 // ties going to the earlier candidate.  Shots with no converged member are
-// queued for LSD.
-// K4: observables Lobs * e mod 2 (paper Sec. II.B), bit-packed AND + popcount.
+// queued for LSD.  The observables Lobs * e mod 2 (paper Sec. II.B) of a shot
+// are formed where its correction is written, here or by LSD.
 #include "internal.h"
 
 namespace vibe {
@@ -52,6 +52,7 @@ __global__ __launch_bounds__(kWave) void select_kernel(DevGraph g, SelectLaunch 
         const uint32_t tw = (uint32_t)__shfl(t, who);
         const uint64_t* src = a.cand + (base + (uint32_t)who) * g.words_n;
         for (uint32_t i = lane; i < g.words_n; i += kWave) out[i] = src[i];
+        write_observables(g, src, a.observables + gshot * g.k, lane);
         if (lane == 0 && a.stats) {
             vibe_shot_stats st;
             st.flags = VIBE_FLAG_BP_CONVERGED | (((sat >> who) & 1ull) ? VIBE_FLAG_SATURATED : 0u);
@@ -78,22 +79,6 @@ __global__ __launch_bounds__(kWave) void select_kernel(DevGraph g, SelectLaunch 
     }
 }
 
-__global__ __launch_bounds__(kWave) void observables_kernel(DevGraph g, const uint64_t* corr,
-                                                            uint64_t shot0, uint32_t n_shots,
-                                                            uint8_t* obs) {
-    const uint32_t shot = blockIdx.x;
-    if (shot >= n_shots) return;
-    const int lane = threadIdx.x;
-    const uint64_t* e = corr + (shot0 + shot) * g.words_n;
-    for (uint32_t r = 0; r < g.k; r++) {
-        const uint64_t* row = g.lobs + (size_t)r * g.words_n;
-        uint32_t par = 0;
-        for (uint32_t i = lane; i < g.words_n; i += kWave) par ^= __popcll(e[i] & row[i]) & 1u;
-        for (int off = kWave / 2; off > 0; off >>= 1) par ^= __shfl_xor(par, off);
-        if (lane == 0) obs[(shot0 + shot) * g.k + r] = (uint8_t)par;
-    }
-}
-
 }  // namespace
 
 int launch_select(const DevGraph& g, const SelectLaunch& a, hipStream_t st) {
@@ -101,15 +86,6 @@ int launch_select(const DevGraph& g, const SelectLaunch& a, hipStream_t st) {
     hipLaunchKernelGGL(select_kernel, dim3(a.n_shots), dim3(kWave), 0, st, g, a);
     hipError_t e = hipGetLastError();
     return e == hipSuccess ? VIBE_OK : hip_fail(e, "select_kernel launch");
-}
-
-int launch_observables(const DevGraph& g, const uint64_t* corrections, uint64_t shot0,
-                       uint32_t n_shots, uint8_t* observables, hipStream_t st) {
-    if (!n_shots || !g.k) return VIBE_OK;
-    hipLaunchKernelGGL(observables_kernel, dim3(n_shots), dim3(kWave), 0, st, g, corrections, shot0,
-                       n_shots, observables);
-    hipError_t e = hipGetLastError();
-    return e == hipSuccess ? VIBE_OK : hip_fail(e, "observables_kernel launch");
 }
 
 }  // namespace vibe
