@@ -1032,6 +1032,7 @@ __device__ __forceinline__ void run_group(const DevGraph& g, const BpLaunch& a, 
 }
 
 #include "bp_compact.h"
+#include "bp_small.h"
 
 // Pass context fields that depend only on the block: lane offsets, the
 // block's global slabs and posterior area.
@@ -1394,6 +1395,43 @@ int bp_grid(const DevGraph& g, bool slab_in_lds) {
 int bp_latency_grid(const DevGraph& g, bool slab_in_lds) {
     if (g.fp64 || g.flood || g.layered || slab_in_lds || g.P != 1 || g.dec_global || g.compact) return 0;
     return bp_grid_for(false, false, false, bp_lds_bytes(g, false), false, false, 1, false, true);
+}
+
+// One lane per shot takes its T x columns steps however few shots there are;
+// one wavefront per shot and member takes its items in turn.  They meet, for
+// 16 members of code capacity and 32 iterations, at about 20 shots of 7
+// columns (105 us), 130 of 19 (270), 500 of 37 (520) and 1300 of 61 (860):
+// shots x members about 6 columns squared.
+bool bp_small_pays(const DevGraph& g, bool slab_in_lds, uint64_t n) {
+    return g.ssched && g.P == 1 && !slab_in_lds && n * g.L >= 6ull * g.scols * g.scols;
+}
+
+int launch_bp_small(const DevGraph& g, BpLaunch a, hipStream_t st) {
+    if (!g.ssched || g.fp64 || g.flood || g.layered || g.m > 64 || g.n > 64 || g.E > kSmallMaxE || !a.stop_on_converge ||
+        a.post_out || !a.cand || !a.weight || !a.qfix)
+        return fail(VIBE_EINVAL, "internal: one lane per shot needs a decode of a small graph");
+    const uint32_t RO = g.sshape >> 4, DM = g.sshape & 15u;
+    const void* fn = RO <= 5 && DM <= 3 ? (const void*)bp_small_kernel<5, 3> : (const void*)bp_small_kernel<7, 4>;
+    const size_t lds = ((size_t)g.E + 1 + g.n) * 256;
+    static std::mutex mu;
+    static std::map<std::tuple<int, const void*, size_t>, int> cache;
+    int dev = 0, grid = 0;
+    (void)hipGetDevice(&dev);
+    {
+        std::lock_guard<std::mutex> lk(mu);
+        int& resident = cache[std::make_tuple(dev, fn, lds)];
+        if (!resident) {
+            int per_cu = 0, cus = 0;
+            if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, fn, kWave, lds) != hipSuccess || per_cu < 1)
+                per_cu = 1;
+            if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) cus = 1;
+            resident = per_cu * cus;
+        }
+        grid = resident;
+    }
+    const uint64_t items = ((uint64_t)a.n_shots + kWave - 1) / kWave * g.L;
+    void* args[] = {const_cast<DevGraph*>(&g), &a};
+    return launch_fn(fn, (int)std::min<uint64_t>((uint64_t)grid, items), lds, args, st);
 }
 
 int launch_bp(const DevGraph& g, const BpLaunch& a, hipStream_t st) {

@@ -580,6 +580,9 @@ extern "C" int vibe_graph_create(uint32_t m, uint32_t n, const uint32_t* h_indpt
     d.ccols = max_col <= 6 ? 6 : 8;
     d.csched = d.crec0 = nullptr;
     d.crow0 = d.cgroup = d.dense0 = nullptr;
+    d.ssched = nullptr;
+    d.scols = d.sshape = 0;
+    d.sfree = 0;
     d.cgroups = 0;
     d.fp64 = fp64 ? 1 : 0;
     d.flood = c.schedule == 1 ? 1 : 0;
@@ -596,6 +599,43 @@ extern "C" int vibe_graph_create(uint32_t m, uint32_t n, const uint32_t* h_indpt
     if (lsd_lds_bytes(d) > 150 * 1024) {
         delete g;
         return fail(VIBE_EUNSUPPORTED, "the per-shot LSD state exceeds 150 KB of LDS");
+    }
+    // one lane per shot (bp_small.h): the members' columns in their order
+    std::vector<uint32_t> s_sched;
+    if (!fp64 && c.schedule == 0 && m && m <= 64 && n <= 64 && E && E <= kSmallMaxE && max_row <= kSmallMaxRow &&
+        max_col <= kSmallMaxCol) {
+        const int RO = max_row <= 6 && max_col <= 3 ? 5 : 7, DM = RO == 5 ? 3 : 4;
+        const uint32_t EW = small_edge_words(RO), CWD = small_col_words(RO, DM);
+        for (uint32_t v = 0; v < n; v++)
+            if (cp[v + 1] == cp[v])
+                d.sfree |= 1ull << v;
+            else
+                d.scols++;
+        d.sshape = (uint32_t)RO << 4 | (uint32_t)DM;
+        s_sched.assign((size_t)c.L * d.scols * CWD, 0);
+        uint32_t* w = s_sched.data();
+        for (uint32_t i = 0; i < c.L; i++)
+            for (uint32_t a = 0; a < n; a++) {
+                const uint32_t v = perms[(size_t)i * n + a], deg = cp[v + 1] - cp[v];
+                if (!deg) continue;
+                w[0] = v | deg << 8;
+                std::memcpy(&w[1], &lam32[v], 4);
+                for (uint32_t j = 0; j < (uint32_t)DM; j++) {
+                    uint32_t* ew = w + 2 + j * EW;
+                    uint32_t oth[8];
+                    uint32_t no = 0, slot = (uint32_t)E, r = 0;
+                    if (j < deg) {
+                        r = ci[cp[v] + j];
+                        slot = ce[cp[v] + j];
+                        for (uint32_t b = h_indptr[r]; b < h_indptr[r + 1]; b++)
+                            if (b != slot) oth[no++] = b;
+                    }
+                    while (no < 8) oth[no++] = (uint32_t)E;
+                    ew[0] = slot * 256u | r << 16;
+                    for (uint32_t q = 0; q < EW - 1; q++) ew[1 + q] = oth[2 * q] * 256u | oth[2 * q + 1] * 256u << 16;
+                }
+                w += CWD;
+            }
     }
     // interleave the schedule fields into chunk records
     const size_t nrec = s_meta.size() / kWave;
@@ -654,7 +694,8 @@ extern "C" int vibe_graph_create(uint32_t m, uint32_t n, const uint32_t* h_indpt
         (rc = upload(h, sched.data(), sched.size(), &d.sched)) ||
         (rc = upload(h, member_chunk.data(), member_chunk.size(), &d.member_chunk)) ||
         (rc = upload(h, layered ? perms : (const uint32_t*)nullptr, layered ? (size_t)c.L * m : 1, &d.cperm)) ||
-        (rc = upload(h, lobs.data(), lobs.size(), &d.lobs)) || (rc = compact_upload())) {
+        (rc = upload(h, lobs.data(), lobs.size(), &d.lobs)) || (rc = compact_upload()) ||
+        (!s_sched.empty() && (rc = upload(h, s_sched.data(), s_sched.size(), &d.ssched)))) {
         free_all(h);
         delete g;
         return rc;

@@ -109,6 +109,11 @@ struct DevGraph {
     const uint32_t* member_chunk; // L + 1: chunk range of each member
     const uint32_t* cperm;        // layered schedule: L x m check orders (else unused)
     const uint64_t* lobs;         // k x words_n, bit-packed observable rows
+    // one lane per shot (bp_small.h); ssched is null where the graph has none
+    const uint32_t* ssched;       // per member and column: see small_col_words
+    uint32_t scols;               // columns with a check
+    uint32_t sshape;              // others per row << 4 | edges per column that the kernel is cut for
+    uint64_t sfree;               // columns without a check
     // compact suffix states (bp_compact.h); csched is null where the graph has none
     int compact;                  // launched with the compact item body: the most edges of a
                                   // column it sums over (6 or 8), with kCompactStream; or 0
@@ -210,6 +215,17 @@ struct BpLaunch {
     int latency;               // the latency variant (every item resident at once)
 };
 int launch_bp(const DevGraph& g, const BpLaunch& a, hipStream_t st);
+// K1 with one lane per shot: whether a decode of n shots of g (as launched)
+// runs it, and the launch (no slabs).
+bool bp_small_pays(const DevGraph& g, bool slab_in_lds, uint64_t n);
+int launch_bp_small(const DevGraph& g, BpLaunch a, hipStream_t st);
+// Limits of the graphs it takes (with m, n <= 64), and its schedule: words of
+// a column: v | deg << 8, lambda, then per edge 4 words (5 others per row) or
+// 5 (7 others): its message's LDS offset | c << 16, then the offsets of the
+// row's other messages, two a word (absent: the slot that holds the clamp).
+constexpr uint32_t kSmallMaxE = 160, kSmallMaxRow = 8, kSmallMaxCol = 4;
+__host__ __device__ constexpr uint32_t small_edge_words(int RO) { return RO <= 5 ? 4u : 5u; }
+__host__ __device__ constexpr uint32_t small_col_words(int RO, int DM) { return RO <= 5 && DM <= 3 ? 16u : 24u; }
 
 // Ragged batching: one BP launch over the items of several requests, each on
 // its own graph (all with the same message precision and schedule).
