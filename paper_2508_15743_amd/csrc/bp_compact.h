@@ -1,5 +1,6 @@
-// The item body of K1 with compact suffix states (FP32, serial schedule,
-// slab in global memory, one shot per wavefront).  Included by bp.hip.
+// The item bodies of K1 with compact row states (FP32, serial or parallel
+// schedule, slab in global memory, one shot per wavefront).  Included by
+// bp.hip.  The serial one first; for the parallel one see FRow.
 //
 // The general body keeps every edge's suffix state (least magnitude and
 // sign parity of the previous sweep's messages on the row's later edges) in
@@ -106,6 +107,7 @@ struct CCtx {
     uint32_t rec_at;              // offset of the records in recs
     uint32_t rec_slab, msk_slab;  // offsets of records and masks in the slab
     uint32_t pre;                 // LDS address of the prefix states (suffix states: 0)
+    uint32_t f_old, f_new;        // flooding: LDS addresses of the rows' values
     uint32_t* res;                // residual s + H e, 32 checks a word
     float* post;
     float* trash;
@@ -155,6 +157,61 @@ __device__ __forceinline__ void crows(const CCtx& x, const CStage& s, CRow& w) {
     if constexpr (!DENSE) w.suf = *lds_at(a);
 }
 
+// The check messages of the lane's column: position q of the column is lane
+// b0 + q.
+template <int DC>
+__device__ __forceinline__ void cgather(uint32_t meta, uint32_t r, uint32_t* rj) {
+#pragma unroll
+    for (int q = 0; q < DC; q++)
+        rj[q] = (uint32_t)__builtin_amdgcn_ds_bpermute((int)(cm_first4(meta) + 4u * (uint32_t)q), (int)r);
+}
+
+// lambda_v + the column's other messages in ascending check order: bit 8 + q
+// of meta says whether position q exists and is another lane (others add an
+// exact zero)
+template <int DC>
+__device__ __forceinline__ float csum(uint32_t meta, uint32_t lam, const uint32_t* rj) {
+    float mu = __uint_as_float(lam);
+    mu += keep_if<8>(rj[0], meta);
+    mu += keep_if<9>(rj[1], meta);
+    mu += keep_if<10>(rj[2], meta);
+    mu += keep_if<11>(rj[3], meta);
+    mu += keep_if<12>(rj[4], meta);
+    mu += keep_if<13>(rj[5], meta);
+    if constexpr (DC > 6) {
+        mu += keep_if<14>(rj[6], meta);
+        mu += keep_if<15>(rj[7], meta);
+    }
+    return mu;
+}
+
+// What follows from a chunk's messages mu (not clamped) and r: posteriors,
+// decisions, the residual and the saturation witness.
+template <bool POST>
+__device__ __forceinline__ void cdecide(const CCtx& x, uint32_t meta, uint32_t k, float mu, uint32_t r, uint32_t v,
+                                        float& satm) {
+    const bool last = (int32_t)meta < 0;      // the column's last lane
+    const float L = mu + __uint_as_float(r);  // L_v there
+    const float both = last ? L : mu;
+    asm("v_max3_f32 %0, %0, |%1|, |%2|" : "+v"(satm) : "v"(mu), "v"(both));
+    const uint64_t dec = __ballot(L <= 0.0f) & __ballot(last);
+    if (dec) {
+        // columns decided 1: flip their checks, keep the mask (a column's
+        // bit is its last lane's)
+        const uint32_t b0 = cm_first4(meta) >> 2, inc = (meta >> 8) & 0xffu;
+        const uint32_t ll = b0 + 31u - (uint32_t)__clz((int)(inc | 1u << (x.lane - b0)));
+        if ((inc || last) && ((dec >> ll) & 1ull)) {
+            const uint32_t c = cm_row4(meta) >> 2;
+            atomicXor(&x.res[c >> 5], 1u << (c & 31u));
+        }
+        if (x.lane == (k & 63u)) bstore<uint64_t>(dec, x.slb, 0u, x.msk_slab + k * 8u);
+    }
+    if constexpr (POST) {
+        float* dst = last ? x.post + v : x.trash + x.lane;
+        *dst = Prec<float>::clamp(L, x.lim);
+    }
+}
+
 // Chunk J of group g (Algorithm 1, serial branch): the operations of
 // sweep_chunk on every message, in the same order.  Its row states are in w
 // and are replaced by those of the group's next chunk, which are read as
@@ -185,25 +242,10 @@ __device__ __forceinline__ void csweep_chunk(const CCtx& x, const CStage& s, CRo
     const uint32_t pre = w.pre;
     const float rr = x.al * __uint_as_float(min_abs(pre, X));
     const uint32_t r = mag_sign(__float_as_uint(rr), pre ^ X);
-    // lambda_v + the column's other messages in ascending check order:
-    // position q of the column is lane b0 + q; bit 8 + q of meta says whether
-    // it exists and is another lane (others add an exact zero)
-    const uint32_t b0x4 = cm_first4(meta);
     uint32_t rj[8];
-#pragma unroll
-    for (int q = 0; q < DC; q++) rj[q] = (uint32_t)__builtin_amdgcn_ds_bpermute((int)(b0x4 + 4u * (uint32_t)q), (int)r);
+    cgather<DC>(meta, r, rj);
     if constexpr (!DENSE && J < 3) crecord<J + 1>(s, w);
-    float mu = __uint_as_float(s.lam[J]);
-    mu += keep_if<8>(rj[0], meta);
-    mu += keep_if<9>(rj[1], meta);
-    mu += keep_if<10>(rj[2], meta);
-    mu += keep_if<11>(rj[3], meta);
-    mu += keep_if<12>(rj[4], meta);
-    mu += keep_if<13>(rj[5], meta);
-    if constexpr (DC > 6) {
-        mu += keep_if<14>(rj[6], meta);
-        mu += keep_if<15>(rj[7], meta);
-    }
+    const float mu = csum<DC>(meta, s.lam[J], rj);
     const uint32_t mb = __float_as_uint(Prec<float>::clamp(mu, x.lim));
     *lds_at(a + x.pre) = mag_sign(min_abs(pre, mb), pre ^ mb);
     out[J] = mb;
@@ -213,26 +255,7 @@ __device__ __forceinline__ void csweep_chunk(const CCtx& x, const CStage& s, CRo
     __builtin_amdgcn_sched_barrier(0);
     if constexpr (J < 3) crows<DENSE, J + 1>(x, s, w);
     __builtin_amdgcn_sched_barrier(0);
-    const bool last = (int32_t)meta < 0;      // the column's last lane
-    const float L = mu + __uint_as_float(r);  // L_v there
-    const float both = last ? L : mu;
-    asm("v_max3_f32 %0, %0, |%1|, |%2|" : "+v"(satm) : "v"(mu), "v"(both));
-    const uint64_t dec = __ballot(L <= 0.0f) & __ballot(last);
-    if (dec) {
-        // columns decided 1: flip their checks, keep the mask (a column's
-        // bit is its last lane's)
-        const uint32_t b0 = b0x4 >> 2, inc = (meta >> 8) & 0xffu;
-        const uint32_t ll = b0 + 31u - (uint32_t)__clz((int)(inc | 1u << (x.lane - b0)));
-        if ((inc || last) && ((dec >> ll) & 1ull)) {
-            const uint32_t c = a >> 2;
-            atomicXor(&x.res[c >> 5], 1u << (c & 31u));
-        }
-        if (x.lane == (k & 63u)) bstore<uint64_t>(dec, x.slb, 0u, x.msk_slab + k * 8u);
-    }
-    if constexpr (POST) {
-        float* dst = last ? x.post + s.v[J] : x.trash + x.lane;
-        *dst = Prec<float>::clamp(L, x.lim);
-    }
+    cdecide<POST>(x, meta, k, mu, r, POST ? s.v[J] : 0u, satm);
     __builtin_amdgcn_sched_barrier(0);
 }
 
@@ -377,9 +400,103 @@ __device__ __forceinline__ void cbackward(const CCtx& x, uint32_t g0, uint32_t g
     }
 }
 
+// The parallel (flooding) schedule: every message of an iteration comes from
+// the previous iteration's, so a check message needs its row's least and
+// next least magnitude and the parity of all signs (Algorithm 1, parallel
+// branch): the least magnitude of the others is the next least for the edge
+// that has the least, and the least for all others.  The rows' values are
+// two words of LDS per check, read for the previous iteration and formed
+// for the next in the same pass; an edge's message stays in its slab slot.
+// Row values: x.f_old, and x.f_old + x.pre; the next: x.f_new, likewise.
+struct FRow {
+    uint32_t o1, o2, n1, n2;
+};
+
+template <int J>
+__device__ __forceinline__ void fold(const CCtx& x, const CStage& s, FRow& w) {
+    const uint32_t a = cm_row4(s.meta[J]);
+    w.o1 = *lds_at(a + x.f_old);
+    w.o2 = *lds_at(a + x.f_old + x.pre);
+}
+
+template <int J>
+__device__ __forceinline__ void fnew(const CCtx& x, const CStage& s, FRow& w) {
+    const uint32_t a = cm_row4(s.meta[J]);
+    w.n1 = *lds_at(a + x.f_new);
+    w.n2 = *lds_at(a + x.f_new + x.pre);
+}
+
+template <int DC, bool POST, int J>
+__device__ __forceinline__ void fsweep_chunk(const CCtx& x, const CStage& s, FRow& w, uint32_t g, bool first,
+                                             u32x4& out, float& satm) {
+    const uint32_t meta = s.meta[J], old = first ? s.lam[J] : s.st[J];
+    const uint32_t mag = fabsf(__uint_as_float(old)) == fabsf(__uint_as_float(w.o1)) ? w.o2 : w.o1;
+    const float rr = x.al * fabsf(__uint_as_float(mag));
+    const uint32_t r = mag_sign(__float_as_uint(rr), w.o1 ^ old);
+    uint32_t rj[8];
+    cgather<DC>(meta, r, rj);
+    if constexpr (J < 3) fold<J + 1>(x, s, w);
+    const float mu = csum<DC>(meta, s.lam[J], rj);
+    const uint32_t mb = __float_as_uint(Prec<float>::clamp(mu, x.lim)), a = cm_row4(meta);
+    *lds_at(a + x.f_new) = mag_sign(min_abs(w.n1, mb), w.n1 ^ mb);
+    *lds_at(a + x.f_new + x.pre) = __float_as_uint(
+        __builtin_amdgcn_fmed3f(fabsf(__uint_as_float(w.n1)), __uint_as_float(w.n2), fabsf(__uint_as_float(mb))));
+    out[J] = mb;
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_sched_barrier(0);
+    if constexpr (J < 3) fnew<J + 1>(x, s, w);
+    __builtin_amdgcn_sched_barrier(0);
+    cdecide<POST>(x, meta, g * 4 + J, mu, r, POST ? s.v[J] : 0u, satm);
+    __builtin_amdgcn_sched_barrier(0);
+}
+
+template <int DC, bool POST, int NT>
+__device__ __forceinline__ void fsweep_group(const CCtx& x, const CStage& s, uint32_t g, bool first, float& satm) {
+    FRow w;
+    u32x4 out;
+    fold<0>(x, s, w);
+    fnew<0>(x, s, w);
+    fsweep_chunk<DC, POST, 0>(x, s, w, g, first, out, satm);
+    fsweep_chunk<DC, POST, 1>(x, s, w, g, first, out, satm);
+    fsweep_chunk<DC, POST, 2>(x, s, w, g, first, out, satm);
+    fsweep_chunk<DC, POST, 3>(x, s, w, g, first, out, satm);
+    bstore4<NT>(out, x.slb, x.lane16, g * kCSlab);
+}
+
+// One iteration over ng groups (an even number), loaded A ahead as csweep
+// (before the first one the slab's words are loaded but not used).
+template <int DC, bool POST, int A, int NT>
+__device__ __forceinline__ void fsweep(const CCtx& x, uint32_t ng, bool first, float& satm) {
+    if (!ng) return;
+    CStage ring[A];
+#pragma unroll
+    for (int d = 0; d < A; d++) {
+        cfetch<true, POST, NT>(x, ring[d], min((uint32_t)d, ng - 1));
+        __builtin_amdgcn_sched_barrier(0);
+    }
+    uint32_t g = 0;
+    for (; g + A <= ng; g += A) {
+#pragma unroll
+        for (int d = 0; d < A; d++) {
+            fsweep_group<DC, POST, NT>(x, ring[d], g + d, first, satm);
+            cfetch<true, POST, NT>(x, ring[d], min(g + d + A, ng - 1));
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    }
+    if constexpr (A > 2) {
+#pragma unroll
+        for (int d = 0; d < A - 2; d += 2) {
+            if (g + d >= ng) break;
+            fsweep_group<DC, POST, NT>(x, ring[d], g + d, first, satm);
+            fsweep_group<DC, POST, NT>(x, ring[d + 1], g + d + 1, first, satm);
+        }
+    }
+}
+
 // One work item, as run_item.  slb: the block's slab (bp_slab_elems words);
 // post: its posteriors.
-template <int DC, int NT>
+template <int DC, int NT, bool FLOOD = false>
 __device__ __forceinline__ void run_item_c(const DevGraph& g, const BpLaunch& a, uint32_t item, unsigned char* lds,
                                            Rsrc slb, float* post) {
     CCtx x;
@@ -431,22 +548,33 @@ __device__ __forceinline__ void run_item_c(const DevGraph& g, const BpLaunch& a,
     }
     const uint32_t c0 = uni(g.member_chunk[mem]), nch = uni(g.member_chunk[mem + 1]) - c0;
     // groups of the member, of which gd .. ng-1 keep their states in the slab
-    const uint32_t cg0 = uni(g.cgroup[mem]), ng = uni(g.cgroup[mem + 1]) - cg0, gd = uni(g.dense0[mem]);
+    const uint32_t cg0 = uni(g.cgroup[mem]), ng = uni(g.cgroup[mem + 1]) - cg0, gd = FLOOD ? 0u : uni(g.dense0[mem]);
     x.sch = make_rsrc(g.csched + (size_t)cg0 * kCSch, ng * kCSch);
     x.osch = make_rsrc(g.sched + (size_t)c0 * rec_bytes(false), nch * rec_bytes(false));
-    x.recs = make_rsrc(g.crec0 + (size_t)cg0 * kCRec, ng * kCRec);
-    x.rec_at = 0;
-    // the initial states of the dense groups (chunks past the last read 0)
-    for (uint32_t q = gd; q < ng; q++) {
-        u32x4 st;
+    if constexpr (!FLOOD) {
+        x.recs = make_rsrc(g.crec0 + (size_t)cg0 * kCRec, ng * kCRec);
+        x.rec_at = 0;
+        // the initial states of the dense groups (chunks past the last read 0)
+        for (uint32_t q = gd; q < ng; q++) {
+            u32x4 st;
 #pragma unroll
-        for (int j = 0; j < 4; j++)
-            st[j] = bload<uint32_t>(x.osch, lane * 4u + rec_init(false), (q * 4 + j) * rec_bytes(false));
-        bstore4<0>(st, slb, x.lane16, q * kCSlab);
+            for (int j = 0; j < 4; j++)
+                st[j] = bload<uint32_t>(x.osch, lane * 4u + rec_init(false), (q * 4 + j) * rec_bytes(false));
+            bstore4<0>(st, slb, x.lane16, q * kCSlab);
+        }
     }
     float* post_out = a.post_out ? reinterpret_cast<float*>(a.post_out) + (size_t)rec * g.n : nullptr;
-    // suffix states before the first sweep: all of the row's initial messages
-    for (uint32_t c = lane; c <= g.m; c += kWave) suf[c] = c < g.m ? g.crow0[c] : 0u;
+    // before the first sweep: all of the row's initial messages
+    for (uint32_t c = lane; c <= g.m; c += kWave) {
+        suf[c] = c < g.m ? g.crow0[c] : 0u;
+        if constexpr (FLOOD) {
+            const uint64_t w = c < g.m ? sb[c >> 6] : 0ull;
+            suf[c] ^= ((uint32_t)(w >> (c & 63u)) & 1u) << 31;
+            pre[c] = c < g.m ? g.crow2[c] : 0u;
+        }
+    }
+    x.f_old = 0u;
+    x.f_new = 2u * x.pre;
 
     uint32_t conv_t = 0, ran = 0;
     bool stopped = false;
@@ -460,14 +588,28 @@ __device__ __forceinline__ void run_item_c(const DevGraph& g, const BpLaunch& a,
         const bool want_post = post_out != nullptr || (a.accumulate_q && t == a.T_run);
         if (want_post)
             for (uint32_t v = lane; v < g.n; v += kWave) post[v] = lamv[v];
+        // prefix states (flooding: the row values of the messages to come)
         for (uint32_t c = lane; c <= g.m; c += kWave) {
             const uint64_t w = c < g.m ? sb[c >> 6] : 0ull;
-            pre[c] = c < g.m ? g.ident32 | ((uint32_t)(w >> (c & 63u)) & 1u) << 31 : 0u;
+            const uint32_t none = c < g.m ? g.ident32 | ((uint32_t)(w >> (c & 63u)) & 1u) << 31 : 0u;
+            if constexpr (FLOOD) {
+                *lds_at(x.f_new + 4u * c) = none;
+                *lds_at(x.f_new + x.pre + 4u * c) = none & kMag;
+            } else {
+                pre[c] = none;
+            }
         }
         for (uint32_t w = lane; w < g.words_m; w += kWave) res[w] = sb[w];
         for (uint32_t k = lane; k < nch; k += kWave) bstore<uint64_t>(0ull, slb, k * 8u, x.msk_slab);
         __syncthreads();
-        if (want_post) {
+        if constexpr (FLOOD) {
+            if (want_post)
+                fsweep<DC, true, kCAhead, NT>(x, ng, t == 1, satm);
+            else
+                fsweep<DC, false, kCAhead, NT>(x, ng, t == 1, satm);
+            x.f_old = x.f_new;
+            x.f_new = 2u * x.pre - x.f_old;
+        } else if (want_post) {
             csweep<DC, false, true, kCAhead, NT>(x, 0, gd, t == 1, satm);
             csweep<DC, true, true, kCAhead, NT>(x, gd, ng, t == 1, satm);
         } else {
@@ -487,7 +629,7 @@ __device__ __forceinline__ void run_item_c(const DevGraph& g, const BpLaunch& a,
             if (!conv_t) conv_t = t;
             if (a.stop_on_converge) break;
         }
-        if (t < a.T_run) {
+        if (!FLOOD && t < a.T_run) {
             for (uint32_t c = lane; c <= g.m; c += kWave) suf[c] = c < g.m ? g.ident32 : 0u;
             __syncthreads();
             cbackward<true, kCAhead, NT>(x, gd, ng);

@@ -329,10 +329,10 @@ extern "C" int vibe_graph_create(uint32_t m, uint32_t n, const uint32_t* h_indpt
     std::vector<float> s_lam32;
     std::vector<double> s_lam64;
     std::vector<uint64_t> init64;
-    // compact suffix states (bp_compact.h): FP32, serial schedule, columns of
-    // at most 8 checks
-    const bool want_compact = !fp64 && c.schedule == 0 && max_col <= 8 && E && m < 8192;
-    std::vector<uint32_t> c_sched, c_rec0, c_row0, c_group(c.L + 1, 0), c_dense0(c.L, 0), c_later(m);
+    // compact item bodies (bp_compact.h): FP32, serial or parallel schedule,
+    // columns of at most 8 checks
+    const bool want_compact = !fp64 && !layered && max_col <= 8 && E && m < 8192;
+    std::vector<uint32_t> c_sched, c_rec0, c_row0, c_row2, c_group(c.L + 1, 0), c_dense0(c.L, 0), c_later(m);
     std::vector<float> c_exp;
     uint64_t c_chunks = 0;
     std::vector<uint32_t> member_chunk(c.L + 1, 0);
@@ -510,7 +510,19 @@ extern "C" int vibe_graph_create(uint32_t m, uint32_t n, const uint32_t* h_indpt
                         }
                         if (vals > 12) rc[2] = rc[3] = 0xffffffffu;
                     }
-                    if (i == 0) c_row0 = running32;
+                    if (i == 0) {
+                        c_row0 = running32;
+                        if (c.schedule == 1) {  // the rows' next least magnitudes
+                            c_row2.assign(m, ident32);
+                            std::vector<uint32_t> least(m, ident32);
+                            for (size_t q = first_slot; q < end_slot; q++) {
+                                if (!((s_meta[q] >> kMetaDegShift) & 15u)) continue;
+                                const uint32_t r = s_meta[q] & 0xffffu, mag = enc32(s_lam32[q]) & 0x7fffffffu;
+                                c_row2[r] = std::min(c_row2[r], std::max(least[r], mag));
+                                least[r] = std::min(least[r], mag);
+                            }
+                        }
+                    }
                     // the first group that keeps its states in the slab
                     // slots: least bytes over the sweep, 64 for a record that
                     // fits, 256 for states in the slots, and for a record
@@ -579,7 +591,7 @@ extern "C" int vibe_graph_create(uint32_t m, uint32_t n, const uint32_t* h_indpt
     d.compact = 0;
     d.ccols = max_col <= 6 ? 6 : 8;
     d.csched = d.crec0 = nullptr;
-    d.crow0 = d.cgroup = d.dense0 = nullptr;
+    d.crow0 = d.crow2 = d.cgroup = d.dense0 = nullptr;
     d.ssched = nullptr;
     d.scols = d.sshape = 0;
     d.sfree = 0;
@@ -674,6 +686,7 @@ extern "C" int vibe_graph_create(uint32_t m, uint32_t n, const uint32_t* h_indpt
         const uint32_t* p[2] = {nullptr, nullptr};
         int r;
         if ((r = upload(h, c_rec0.data(), c_rec0.size(), &p[0])) || (r = upload(h, c_row0.data(), c_row0.size(), &d.crow0)) ||
+            (r = upload(h, c_row2.data(), c_row2.size(), &d.crow2)) ||
             (r = upload(h, c_group.data(), c_group.size(), &d.cgroup)) ||
             (r = upload(h, c_dense0.data(), c_dense0.size(), &d.dense0)) ||
             (r = upload(h, c_sched.data(), c_sched.size(), &p[1])))

@@ -114,7 +114,7 @@ struct DevGraph {
     uint32_t scols;               // columns with a check
     uint32_t sshape;              // others per row << 4 | edges per column that the kernel is cut for
     uint64_t sfree;               // columns without a check
-    // compact suffix states (bp_compact.h); csched is null where the graph has none
+    // compact item bodies (bp_compact.h); csched is null where the graph has none
     int compact;                  // launched with the compact item body: the most edges of a
                                   // column it sums over (6 or 8), with kCompactStream; or 0
     int ccols;                    // what compact is set to
@@ -125,6 +125,7 @@ struct DevGraph {
                                   // its last lane.  Unused slots: c = m, their own first lane
     const unsigned char* crec0;   // per chunk: the record of the initial messages (64 bytes)
     const uint32_t* crow0;        // m: row states of all initial messages
+    const uint32_t* crow2;        // parallel schedule: m next least magnitudes of them
     const uint32_t* cgroup;       // L + 1: group range of each member
     const uint32_t* dense0;       // L: its first group whose states stay in the slab slots (even)
 };
@@ -285,10 +286,12 @@ __host__ __device__ inline size_t bp_post_elems(const DevGraph& g) {
 __host__ __device__ inline uint32_t bp_slab_elems(const DevGraph& g) {
     return g.compact ? (g.cgroups * (4 * kWave + 4 * 16 + 4 * 2) + 63) / 64 * 64 : g.max_chunks * kWave;
 }
-// LDS of a compact item body's row states, or of the decision bitmap formed
+// LDS of a compact item body's row states (two words per check, four on the
+// parallel schedule), or of the decision bitmap formed
 // over them, in 8-byte words
 __host__ __device__ inline uint32_t bp_compact_rows(const DevGraph& g) {
-    return g.m + 1 > g.words_n ? g.m + 1 : g.words_n;
+    const uint32_t rows = (g.m + 1) * (g.flood ? 2u : 1u);
+    return rows > g.words_n ? rows : g.words_n;
 }
 // BP work items of n shots: (member, group of P shots)
 inline uint64_t bp_items(const DevGraph& g, uint64_t n) { return (n + g.P - 1) / g.P * g.L; }

@@ -169,3 +169,41 @@ def test_server_serves_what_only_the_general_body_fits(torch_cuda):
     assert srv.info()["peak_bytes"] <= hi
     srv.close()
     G.close()
+
+
+@pytest.mark.parametrize("key", ["circuit d=7", "columns of 6", "columns of 8", "equal priors", "priors above 1/2"])
+def test_compact_parallel_equals_general(torch_cuda, key):
+    """The parallel schedule's one-pass body (a row's two least magnitudes)
+    against the general one, which ragged launches run; posteriors of every
+    iteration's last sweep against the general FP64 body within FP32's
+    rounding (1e-4 of max(|L|, 1), where no decision is near a tie)."""
+    import paper_2508_15743_amd as P
+
+    torch = torch_cuda
+    print(f"parallel, case {key}", flush=True)
+    mk, L, M, T, _ = CASES[key]
+    dem = mk()
+    for L in (1, 3):
+        perms = permutations(dem.n, L, 60)
+        G = P.Graph.from_dem(dem, perms, L=L, M=1, T_max=T, schedule="parallel")
+        synd = sample(dem, 203, 61).syndromes
+        synd[3] = 0
+        s = torch.from_numpy(synd).to("cuda:0")
+        rt = P.Runtime()
+        want = rt.decode([(G, s)])[0]
+        _same(torch, G.decode(s), want)
+        G.set_launch(slab_in_lds=0, grid=7)
+        _same(torch, G.decode(s), want)
+        G.set_launch(slab_in_lds=0)
+        _same(torch, G.decode(s, noalloc=True), want)
+        rt.close()
+        G64 = P.Graph.from_dem(dem, perms, L=L, M=1, T_max=T, schedule="parallel", message_bits=64)
+        _, p32, e32 = G.bp_ensemble(s[:40], T_run=3, stop=False)
+        _, p64, e64 = G64.bp_ensemble(s[:40], T_run=3, stop=False)
+        err = (p32.double() - p64).abs() / p64.abs().clamp(min=1.0)
+        assert float(err.max()) <= 1e-4
+        if not bool((p64.abs() < 1e-3).any()):
+            assert torch.equal(e32, e64)
+        torch.cuda.synchronize()
+        G.close()
+        G64.close()
