@@ -58,9 +58,15 @@ template <int AUX>
 __device__ __forceinline__ u32x4 bload4(Rsrc r, uint32_t voff, uint32_t soff) {
     return __builtin_amdgcn_raw_buffer_load_b128(r, (int)voff, (int)soff, AUX);
 }
+// A 16-byte store reads its data registers for some cycles after it issues:
+// an instruction right behind it that writes them changed what was stored
+// (seen: four lanes of each row of 16, where two wavefronts contend).  The
+// compiler leaves the two wait states out where soffset is a register, so
+// they are placed here, with the data kept until after them.
 template <int AUX>
 __device__ __forceinline__ void bstore4(u32x4 v, Rsrc r, uint32_t voff, uint32_t soff) {
     __builtin_amdgcn_raw_buffer_store_b128(v, r, (int)voff, (int)soff, AUX);
+    asm volatile("s_nop 1" ::"v"(v));
 }
 
 // min(|a|, |b|) of two finite floats, as bits
