@@ -53,7 +53,7 @@ BYTES_PER_EDGE_UPDATE = 8.0
 
 
 PROFILE = os.path.join(ROOT, "profiles", "bp_ensemble_kernel_circuit_d9_r9_p1e-3.txt")
-KERNEL_SOURCES = ("bp.hip", "bp_compact.h", "bp_small.h", "internal.h", "graph.hip")
+KERNEL_SOURCES = ("bp.hip", "bp_compact.h", "bp_small.h", "bp_layered.h", "internal.h", "graph.hip")
 GRAD_PROFILE = os.path.join(ROOT, "profiles", "bp_grad_kernel_circuit_d5_r5_p1e-3.txt")
 GRAD_SOURCES = ("grad.hip", "internal.h", "graph.hip")
 

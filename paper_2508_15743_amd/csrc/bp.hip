@@ -1033,6 +1033,7 @@ __device__ __forceinline__ void run_group(const DevGraph& g, const BpLaunch& a, 
 
 #include "bp_compact.h"
 #include "bp_small.h"
+#include "bp_layered.h"
 
 // Pass context fields that depend only on the block: lane offsets, the
 // block's global slabs and posterior area.
@@ -1156,6 +1157,30 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(4))) void
             run_item_c<DC, NT>(g, a, item - segs[j].item0, lds, x.slb, post);
         else
             run_item<float, false, false, false, false, kDepth>(g, a, item - segs[j].item0, lds, x);
+        __syncthreads();
+    }
+}
+
+// The layered schedule with the posteriors in LDS (bp_layered.h).
+template <int NR, int W>
+__global__ __launch_bounds__(kWave * W) void bp_layered_kernel(DevGraph g, BpLaunch a) {
+    extern __shared__ __align__(16) unsigned char lds[];
+    const uint32_t slab_elems = bp_slab_elems(g);
+    const Rsrc slb = make_rsrc(reinterpret_cast<uint32_t*>(a.slab) + (size_t)blockIdx.x * slab_elems, slab_elems * 4u);
+    float* post = reinterpret_cast<float*>(a.post_slab) + (size_t)blockIdx.x * bp_post_elems(g);
+    const uint32_t n_items = a.n_shots * g.L;
+    // the block's ticket, behind the item's LDS
+    uint32_t* ticket = reinterpret_cast<uint32_t*>(lds + bp_layered_lds(g) - 8);
+    for (;;) {
+        if (threadIdx.x < kWave) {
+            const uint32_t got = wave_ticket(a.counter, 1u);
+            if (threadIdx.x == 0) *ticket = got;
+        }
+        __syncthreads();
+        const uint32_t item = uni(*ticket);
+        __syncthreads();
+        if (item >= n_items) break;
+        run_item_l<NR, W>(g, a, item, lds, slb, post);
         __syncthreads();
     }
 }
@@ -1293,6 +1318,12 @@ const void* multi_kernel_for(bool ragged, uint32_t P) {
     return P == 2 ? (const void*)bp_multi_kernel<F, 2, DG> : (const void*)bp_multi_kernel<F, 4, DG>;
 }
 
+template <int W>
+const void* layered_kernel_for(int nr) {
+    return nr == 1 ? (const void*)bp_layered_kernel<1, W>
+                   : nr == 2 ? (const void*)bp_layered_kernel<2, W> : (const void*)bp_layered_kernel<4, W>;
+}
+
 // compact: the item body's column width (6 or 8), with kCompactStream where
 // the slab is streamed
 template <int NT>
@@ -1308,7 +1339,7 @@ const void* compact_kernel_for(bool ragged, int compact, bool flood) {
 // non-layered items; the slab in global memory)
 const void* kernel_for(bool fp64, bool flood, bool slab_in_lds, bool ragged, bool layered = false, uint32_t P = 1,
                        bool dg = false, bool latency = false, int compact = 0) {
-    if (compact)
+    if (compact && !layered)
         return compact & kCompactStream ? compact_kernel_for<kStream>(ragged, compact, flood)
                                         : compact_kernel_for<0>(ragged, compact, flood);
     // the latency variant: FP32, serial schedule, global slab, one shot per
@@ -1321,7 +1352,10 @@ const void* kernel_for(bool fp64, bool flood, bool slab_in_lds, bool ragged, boo
         if (fp64) return dg ? multi_kernel_for<double, true>(ragged, P) : multi_kernel_for<double, false>(ragged, P);
         return dg ? multi_kernel_for<float, true>(ragged, P) : multi_kernel_for<float, false>(ragged, P);
     }
-    // the layered schedule: one request at a time, slab in global memory
+    // the layered schedule: one request at a time, slab in global memory,
+    // posteriors in LDS (compact) or behind the messages
+    if (layered && !ragged && compact)
+        return compact >= kLayeredWaves * 8 ? layered_kernel_for<kLayeredWaves>(compact & 7) : layered_kernel_for<1>(compact & 7);
     if (layered && !ragged) return fp64 ? (const void*)bp_ensemble_kernel<double, false, false, true>
                                         : (const void*)bp_ensemble_kernel<float, false, false, true>;
     if (fp64)
@@ -1331,12 +1365,12 @@ const void* kernel_for(bool fp64, bool flood, bool slab_in_lds, bool ragged, boo
                  : kernel_for_t<float, false>(slab_in_lds, ragged, layered, dg);
 }
 
-int launch_fn(const void* fn, int grid, size_t lds, void** args, hipStream_t st) {
+int launch_fn(const void* fn, int grid, size_t lds, void** args, hipStream_t st, int threads = kWave) {
     if (lds > 64 * 1024) {
         hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
         if (e != hipSuccess) return hip_fail(e, "hipFuncSetAttribute(bp)");
     }
-    hipError_t e = hipLaunchKernel(fn, dim3(grid), dim3(kWave), args, lds, st);
+    hipError_t e = hipLaunchKernel(fn, dim3(grid), dim3(threads), args, lds, st);
     if (e != hipSuccess) return hip_fail(e, "bp kernel launch");
     e = hipGetLastError();
     if (e != hipSuccess) return hip_fail(e, "bp kernel launch");
@@ -1345,12 +1379,17 @@ int launch_fn(const void* fn, int grid, size_t lds, void** args, hipStream_t st)
 
 }  // namespace
 
+// threads of a block: one wavefront, or those of the layered form with the
+// posteriors in LDS
+static int bp_threads(const DevGraph& g) { return g.layered && g.compact ? (g.compact >> 3) * kWave : kWave; }
+
 int bp_slabs(const DevGraph& g) { return g.flood && !g.compact ? 2 : 1; }
 
 size_t bp_lds_bytes(const DevGraph& g, bool slab_in_lds) {
     const size_t mb = g.fp64 ? 8 : 4;
     // compact: syndrome, residual, two row states per check and for the
     // dummy check; the decision bitmap is formed over the row states
+    if (g.compact && g.layered) return bp_layered_lds(g);
     if (g.compact && !slab_in_lds)
         return 16 * (size_t)g.words_m + 8 * (size_t)bp_compact_rows(g);
     // per shot of the wavefront: syndrome, residual, decisions (unless in
@@ -1383,7 +1422,8 @@ int bp_grid_for(bool fp64, bool flood, bool slab_in_lds, size_t lds_bytes, bool 
     hipDeviceProp_t prop;
     if (hipGetDeviceProperties(&prop, dev) != hipSuccess) return 0;
     int per_cu = 0;
-    hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, fn, kWave, lds_bytes);
+    hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, fn, layered && compact ? (compact >> 3) * kWave : kWave,
+                                                                lds_bytes);
     if (e != hipSuccess || per_cu < 1) per_cu = 1;
     if (per_cu > 32) per_cu = 32;
     const int grid = per_cu * prop.multiProcessorCount;
@@ -1464,7 +1504,7 @@ int launch_bp(const DevGraph& g, const BpLaunch& a, hipStream_t st) {
                                  "and stop on convergence");
     if (g.dec_global && (g.layered || in_lds))
         return fail(VIBE_EINVAL, "internal: decisions in global memory need a chunked schedule and a global slab");
-    if (g.compact && (g.fp64 || g.layered || in_lds || g.P != 1 || !g.csched || g.dec_global))
+    if (g.compact && !g.layered && (g.fp64 || in_lds || g.P != 1 || !g.csched || g.dec_global))
         return fail(VIBE_EINVAL, "internal: the compact item bodies need FP32, a chunked schedule, a global slab and "
                                  "one shot per wavefront");
     if (a.latency && !bp_latency_grid(g, in_lds))
@@ -1472,7 +1512,7 @@ int launch_bp(const DevGraph& g, const BpLaunch& a, hipStream_t st) {
                                  "one shot per wavefront and decisions in LDS");
     return launch_fn(kernel_for(g.fp64 != 0, g.flood != 0, in_lds, false, g.layered != 0, g.P, g.dec_global != 0,
                                 a.latency != 0, g.compact),
-                     a.grid, bp_lds_bytes(g, in_lds), args, st);
+                     a.grid, bp_lds_bytes(g, in_lds), args, st, bp_threads(g));
 }
 
 int launch_bp_ragged(const RaggedLaunch& r, hipStream_t st) {

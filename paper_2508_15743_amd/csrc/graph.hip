@@ -142,7 +142,9 @@ int build_multi_schedule(vibe_graph* G, uint32_t P) {
 
 DevGraph compact_view(DevGraph d) {
     d.compact = 0;
-    if (d.csched && d.P == 1) {
+    if (d.layered) {
+        if (d.lcols) d.compact = d.ccols;
+    } else if (d.csched && d.P == 1) {
         d.compact = d.ccols;
         d.dec_global = 0;  // its decisions are masks in global memory in any case
     }
@@ -593,6 +595,8 @@ extern "C" int vibe_graph_create(uint32_t m, uint32_t n, const uint32_t* h_indpt
     d.csched = d.crec0 = nullptr;
     d.crow0 = d.crow2 = d.cgroup = d.dense0 = nullptr;
     d.ssched = nullptr;
+    d.lcols = d.lorder = nullptr;
+    d.lgroups = 0;
     d.scols = d.sshape = 0;
     d.sfree = 0;
     d.cgroups = 0;
@@ -611,6 +615,60 @@ extern "C" int vibe_graph_create(uint32_t m, uint32_t n, const uint32_t* h_indpt
     if (lsd_lds_bytes(d) > 150 * 1024) {
         delete g;
         return fail(VIBE_EUNSUPPORTED, "the per-shot LSD state exceeds 150 KB of LDS");
+    }
+    // layered sweep with the posteriors in LDS (bp_layered.h): FP32, rows of
+    // at most 256 edges, posteriors within a workgroup's 160 KB
+    std::vector<uint32_t> l_cols, l_order;
+    if (layered && !fp64 && m && max_row <= 256 && bp_layered_lds(d) <= 160 * 1024) {
+        const uint32_t NR = max_row <= 64 ? 1 : max_row <= 128 ? 2 : 4;
+        const uint32_t W = 16 * bp_layered_lds(d) > 160 * 1024 ? kLayeredWaves : 1;
+        d.ccols = (int)(NR | W << 3);
+        l_cols.assign((size_t)(m + 1) * 64 * NR, 4u * n);
+        for (uint32_t r = 0; r < m; r++)
+            for (uint32_t a = h_indptr[r]; a < h_indptr[r + 1]; a++) {
+                const uint32_t q = a - h_indptr[r];
+                l_cols[((size_t)r * 64 + q % 64) * NR + q / 64] = 4u * h_indices[a];
+            }
+        // the checks that share a column with each check
+        std::vector<uint32_t> near, nptr(1, 0), mark(m, UINT32_MAX);
+        for (uint32_t r = 0; r < m; r++) {
+            mark[r] = r;
+            for (uint32_t a = h_indptr[r]; a < h_indptr[r + 1]; a++)
+                for (uint32_t j = cp[h_indices[a]]; j < cp[h_indices[a] + 1]; j++)
+                    if (mark[ci[j]] != r) {
+                        mark[ci[j]] = r;
+                        near.push_back(ci[j]);
+                    }
+            nptr.push_back((uint32_t)near.size());
+        }
+        // a check's level: one more than that of the checks before it in the
+        // member's order that share a column; two of a level share none.
+        // Levels count from 1: a check not yet met has level 0.
+        std::vector<uint32_t> lev((size_t)c.L * m, 0);
+        std::vector<std::vector<uint32_t>> first(c.L);  // first group of each level, then the end
+        for (uint32_t i = 0; i < c.L; i++) {
+            uint32_t* l = lev.data() + (size_t)i * m;
+            std::vector<uint32_t> size(1, 0);
+            for (uint32_t a = 0; a < m; a++) {
+                const uint32_t r = perms[(size_t)i * m + a];
+                uint32_t x = 0;
+                for (uint32_t b = nptr[r]; b < nptr[r + 1]; b++) x = std::max(x, l[near[b]]);
+                l[r] = x + 1;
+                if (size.size() <= x) size.resize(x + 1, 0);
+                size[x]++;
+            }
+            first[i].assign(1, 0);
+            for (uint32_t q : size) first[i].push_back(first[i].back() + (q + W - 1) / W);
+            d.lgroups = std::max(d.lgroups, first[i].back());
+        }
+        l_order.assign((size_t)c.L * d.lgroups * W, m);
+        for (uint32_t i = 0; i < c.L; i++) {
+            for (uint32_t& f : first[i]) f *= W;
+            for (uint32_t a = 0; a < m; a++) {
+                const uint32_t r = perms[(size_t)i * m + a];
+                l_order[(size_t)i * d.lgroups * W + first[i][lev[(size_t)i * m + r] - 1]++] = r;
+            }
+        }
     }
     // one lane per shot (bp_small.h): the members' columns in their order
     std::vector<uint32_t> s_sched;
@@ -708,6 +766,8 @@ extern "C" int vibe_graph_create(uint32_t m, uint32_t n, const uint32_t* h_indpt
         (rc = upload(h, member_chunk.data(), member_chunk.size(), &d.member_chunk)) ||
         (rc = upload(h, layered ? perms : (const uint32_t*)nullptr, layered ? (size_t)c.L * m : 1, &d.cperm)) ||
         (rc = upload(h, lobs.data(), lobs.size(), &d.lobs)) || (rc = compact_upload()) ||
+        (!l_cols.empty() && ((rc = upload(h, l_cols.data(), l_cols.size(), &d.lcols)) ||
+                             (rc = upload(h, l_order.data(), l_order.size(), &d.lorder)))) ||
         (!s_sched.empty() && (rc = upload(h, s_sched.data(), s_sched.size(), &d.ssched)))) {
         free_all(h);
         delete g;

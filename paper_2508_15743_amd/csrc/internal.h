@@ -77,6 +77,11 @@ __host__ __device__ inline B rs_combine(B a, B b) {
 // streamed (in a ragged launch, of any segment)
 constexpr int kCompactStream = 16;
 
+// wavefronts per item of the layered form with the posteriors in LDS, where
+// fewer than 16 items fit a CU (else 1).  4 and 8: d = 9 circuit graph, 1 shot
+// 2.26 and 1.91 ms, 200 shots 22.6 and 22.4; d = 11 4.20 and 3.38, 84 and 70.
+constexpr int kLayeredWaves = 8;
+
 // Everything a kernel needs to know about a resident graph (passed by value).
 struct DevGraph {
     uint32_t m, n, k, L, M, T;
@@ -107,6 +112,11 @@ struct DevGraph {
     const unsigned char* sched;   // chunk records of all members, see above (W = 64 / P
                                   // entries per field for the recut schedules)
     const uint32_t* member_chunk; // L + 1: chunk range of each member
+    const uint32_t* lcols;        // layered, FP32, posteriors in LDS: per check (and the empty
+                                  // check m) [64][ccols] 4 * column, padded with 4 n; else null
+    const uint32_t* lorder;       // then: L x lgroups x W: the member's checks in groups of W that
+    uint32_t lgroups;             // share no column (m: none), in an order that keeps the member's
+                                  // for checks that share one
     const uint32_t* cperm;        // layered schedule: L x m check orders (else unused)
     const uint64_t* lobs;         // k x words_n, bit-packed observable rows
     // one lane per shot (bp_small.h); ssched is null where the graph has none
@@ -116,7 +126,9 @@ struct DevGraph {
     uint64_t sfree;               // columns without a check
     // compact item bodies (bp_compact.h); csched is null where the graph has none
     int compact;                  // launched with the compact item body: the most edges of a
-                                  // column it sums over (6 or 8), with kCompactStream; or 0
+                                  // column it sums over (6 or 8), with kCompactStream; on the
+                                  // layered schedule, for the form with the posteriors in LDS, the
+                                  // edges per lane (1, 2 or 4) and 8 times its wavefronts; or 0
     int ccols;                    // what compact is set to
     uint32_t cgroups;             // largest group count of a member (four chunks each, even)
     const unsigned char* csched;  // per group: meta[64][4], lambda[64][4].  meta: bits 0-7 four
@@ -280,11 +292,18 @@ __host__ __device__ inline size_t bp_post_elems(const DevGraph& g) {
     return bp_post_head(g) + ((size_t)g.max_chunks + (size_t)g.P * g.words_n) * (g.fp64 ? 1 : 2);
 }
 // message slab of one BP block (one of bp_slabs), in message-precision
-// elements; with compact suffix states: per group of four chunks the
+// elements; with a compact item body: per group of four chunks the
 // messages, then per group the records, then per chunk a decision mask, in
-// all a multiple of 256 bytes
+// all a multiple of 256 bytes; layered with the posteriors in LDS: a padded
+// row of messages per check
 __host__ __device__ inline uint32_t bp_slab_elems(const DevGraph& g) {
+    if (g.compact && g.layered) return (g.m + 1) * 64u * (uint32_t)(g.compact & 7);
     return g.compact ? (g.cgroups * (4 * kWave + 4 * 16 + 4 * 2) + 63) / 64 * 64 : g.max_chunks * kWave;
+}
+// LDS of a layered item with its posteriors in LDS: syndrome, residual,
+// decisions, posteriors, two control words and the block's ticket
+__host__ __device__ inline size_t bp_layered_lds(const DevGraph& g) {
+    return 8 * (2 * (size_t)g.words_m + g.words_n) + (4 * ((size_t)g.n + 1 + 2) + 7) / 8 * 8 + 8;
 }
 // LDS of a compact item body's row states (two words per check, four on the
 // parallel schedule), or of the decision bitmap formed
