@@ -1,7 +1,10 @@
 // K1: the ensemble of serial-V min-sum decoders (paper Appendix A, Algorithm 1;
 // ensemble and correction limit, Sec. III.D).
 //
-// One wavefront decodes one work item = (shot, member).
+// One wavefront decodes one work item = (shot, member).  This is the general
+// form; FP32 graphs run one that moves fewer bytes (bp_compact.h), small ones
+// one lane per item (bp_small.h), and the layered schedule one with the
+// posteriors in LDS (bp_layered.h).
 //
 // Exact serial sweep without row rescans.  When column v is visited, the
 // edges of a row that come before v in the sweep carry this sweep's messages
