@@ -22,10 +22,10 @@
 // m1 takes m2, the others m1.
 //
 // Bound by each check's chain (0.4 us a group) and by instruction issue.  With
-// 32 members: d = 9 circuit graph, 1 shot 21.2 -> 1.9 ms, 200 shots 81.8 ->
-// 22.4 ms; d = 5, 2000 shots 24.6 -> 15.3 ms; d = 11, 200 shots 216 -> 70 ms;
-// one wavefront per item 49 ms on the 200 shots of d = 9, two checks
-// interleaved in it 45.6.
+// 32 members: d = 9 circuit graph, 1 shot 21.2 -> 1.9 ms, a decode of 200
+// shots 86.7 -> 25.9 ms (this kernel 81.8 -> 22.4); d = 5, 2000 shots 24.6 ->
+// 15.3 ms; d = 11, 200 shots 216 -> 70 ms; one wavefront per item 49 ms on the
+// 200 shots of d = 9, two checks interleaved in it 45.6.
 
 constexpr uint32_t kLAhead = 4;
 
