@@ -106,7 +106,8 @@ __device__ __forceinline__ uint32_t cm_first4(uint32_t meta) { return meta & 0xf
 
 struct CCtx {
     Rsrc sch;    // the member's compact schedule
-    Rsrc osch;   // the member's chunk records (columns, initial states)
+    Rsrc osch;   // the member's chunk records (columns, initial states), addressed by
+                 // lane offsets only: padding chunks lie past its end
     Rsrc slb;    // the block's slab: messages (states in dense chunks), then the records and
                  // the decision mask of each chunk
     Rsrc recs;   // where the sweep reads its records: the slab, or those of the initial messages
@@ -139,7 +140,7 @@ __device__ __forceinline__ void cfetch(const CCtx& x, CStage& s, uint32_t g) {
         s.rec = __builtin_amdgcn_raw_buffer_load_b32(x.recs, (int)x.lane4, (int)(x.rec_at + g * kCRec), NT);
     if constexpr (POST) {
 #pragma unroll
-        for (int j = 0; j < 4; j++) s.v[j] = bload<uint32_t>(x.osch, x.lane4 + kRecV, (g * 4 + j) * rec_bytes(false));
+        for (int j = 0; j < 4; j++) s.v[j] = bload<uint32_t>(x.osch, x.lane4 + kRecV + (g * 4 + j) * rec_bytes(false), 0);
     }
 }
 
@@ -237,7 +238,7 @@ __device__ __forceinline__ void csweep_chunk(const CCtx& x, const CStage& s, CRo
         X = mag_sign(mag, w.suf ^ sgn);
         asm("" : "+v"(X));
         if (w.rc == ~0ull) {  // more records than fit: the states are in the slots
-            X = first ? bload<uint32_t>(x.osch, x.lane4 + rec_init(false), k * rec_bytes(false))
+            X = first ? bload<uint32_t>(x.osch, x.lane4 + rec_init(false) + k * rec_bytes(false), 0)
                       : bload<uint32_t>(x.slb, x.lane16 + 4u * J, g * kCSlab);
             // waited for here, so that the next groups' loads in flight are
             // not waited for where the paths join
@@ -560,12 +561,14 @@ __device__ __forceinline__ void run_item_c(const DevGraph& g, const BpLaunch& a,
     if constexpr (!FLOOD) {
         x.recs = make_rsrc(g.crec0 + (size_t)cg0 * kCRec, ng * kCRec);
         x.rec_at = 0;
-        // the initial states of the dense groups (chunks past the last read 0)
+        // the initial states of the dense groups.  Chunks past the member's
+        // last read 0: the chunk is part of the lane's offset, which the
+        // resource's size bounds; a scalar offset is outside that check
         for (uint32_t q = gd; q < ng; q++) {
             u32x4 st;
 #pragma unroll
             for (int j = 0; j < 4; j++)
-                st[j] = bload<uint32_t>(x.osch, lane * 4u + rec_init(false), (q * 4 + j) * rec_bytes(false));
+                st[j] = bload<uint32_t>(x.osch, x.lane4 + rec_init(false) + (q * 4 + j) * rec_bytes(false), 0);
             bstore4<0>(st, slb, x.lane16, q * kCSlab);
         }
     }
