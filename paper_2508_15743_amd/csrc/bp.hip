@@ -1462,13 +1462,8 @@ int bp_latency_grid(const DevGraph& g, bool slab_in_lds) {
     return bp_grid_for(false, false, false, bp_lds_bytes(g, false), false, false, 1, false, true);
 }
 
-// One lane per shot takes its T x columns steps however few shots there are;
-// one wavefront per shot and member takes its items in turn.  They meet, for
-// 16 members of code capacity and 32 iterations, at about 20 shots of 7
-// columns (105 us), 130 of 19 (270), 500 of 37 (520) and 1300 of 61 (860):
-// shots x members about 6 columns squared.
 bool bp_small_pays(const DevGraph& g, bool slab_in_lds, uint64_t n) {
-    return g.ssched && g.P == 1 && !slab_in_lds && n * g.L >= 6ull * g.scols * g.scols;
+    return g.ssched && g.P == 1 && !slab_in_lds && n * g.L >= g.sitems;
 }
 
 int launch_bp_small(const DevGraph& g, BpLaunch a, hipStream_t st) {
@@ -1490,7 +1485,9 @@ int launch_bp_small(const DevGraph& g, BpLaunch a, hipStream_t st) {
             if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, fn, kWave, lds) != hipSuccess || per_cu < 1)
                 per_cu = 1;
             if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) cus = 1;
-            resident = per_cu * cus;
+            // the same number on each of the four SIMDs, and no more than two,
+            // which issue as much as more would
+            resident = (per_cu > 8 ? 8 : per_cu > 4 ? per_cu & ~3 : per_cu) * cus;
         }
         grid = resident;
     }

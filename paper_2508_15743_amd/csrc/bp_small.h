@@ -12,17 +12,65 @@
 // word each in its lane's registers.  A check message is formed from the
 // row's other messages as they stand, which is the serial schedule itself.
 //
-// The wavefront runs until each of its shots has converged or reached the
-// iteration limit.  The correction limit is not looked at: among 64 shots
-// some run to the limit in any case, and stopping a member that cannot be
-// among the first M changes no result.  For the same reason every member
-// without convergence adds its normalised posterior: the sum is only read
-// for shots in which none converged.
+// A wavefront has an even share of the member's shots.  A lane whose shot is
+// decided (converged, out of the first M, or at the iteration limit) waits
+// until there are kSmallRefill of them; then their outputs are written and
+// they take the next shots of the share.  So the work is that of the shots,
+// and only the last ones leave lanes idle.  Where 64 shots were taken and run
+// until the last was decided, one that ran to the limit held all lanes: d = 9
+// (61 columns), p = 0.01, T = 64, 20000 shots of 16 members took 16.0 ms, one
+// wavefront per item 4.4, this form 2.3; at p = 0.12, where many reach the
+// limit, 17.3, 38.7 and 19.3 ms.
+//
+// The correction limit: when it takes shots and on every eighth iteration, a
+// wavefront counts the members that precede its own from each shot's
+// convergence masks.  Looking on every iteration cost 0.25 us of 3 (7 columns).
 //
 // Bound by instruction issue, about 200 per column and 64 shots, scalar ones
-// among them (0.45 us a column): d = 5 code capacity, 16 members, 20000 shots
-// 832 us against 4.27 ms with one wavefront per shot and member.  Loading the
-// next column's description during the current one's work gained nothing.
+// among them (0.45 us a column): d = 5 code capacity, 16 members, p = 0.05,
+// T = 32, 10000 shots 374 us against 2.29 ms with one wavefront per shot and
+// member.  Loading the next column's description during the current one's work
+// gained nothing.
+
+// idle lanes at which a wavefront writes the outputs of decided shots and
+// starts new ones, which costs the same however many there are
+constexpr int kSmallRefill = 16;
+
+// bit b of the result: byte b of w is not 0
+__device__ __forceinline__ uint32_t nonzero_bytes(uint32_t w) {
+    const uint32_t x = ((((w & 0x7f7f7f7fu) + 0x7f7f7f7fu) | w) & 0x80808080u) >> 7;
+    return (x * 0x10204080u) >> 28;
+}
+
+// Members converged by iteration t (0: none are looked at).
+__device__ __forceinline__ uint32_t converged_upto(const uint64_t* cmask, uint32_t t) {
+    uint32_t cnt = 0;
+    for (uint32_t i = 1; __ballot(i <= t); i += 16) {
+        uint64_t m[16];
+#pragma unroll
+        for (uint32_t j = 0; j < 16; j++) m[j] = load_mask(&cmask[min(i + j, (uint32_t)kMaxT)]);
+#pragma unroll
+        for (uint32_t j = 0; j < 16; j++) cnt += i + j <= t ? (uint32_t)__popcll(m[j]) : 0u;
+    }
+    return cnt;
+}
+
+// The m <= 64 syndrome bytes of a shot as bits.
+__device__ __forceinline__ uint64_t syndrome_bits(const uint8_t* s, uint32_t m) {
+    uint64_t b = 0;
+    if (m < 4) {
+        for (uint32_t c = 0; c < m; c++) b |= (uint64_t)(s[c] != 0 ? 1u : 0u) << c;
+        return b;
+    }
+#pragma unroll 4
+    for (uint32_t c = 0; c < m; c += 4) {
+        const uint32_t at = min(c, m - 4);  // the last four may overlap
+        uint32_t w;
+        __builtin_memcpy(&w, s + at, 4);
+        b |= (uint64_t)nonzero_bytes(w) << at;
+    }
+    return b;
+}
 
 template <int RO, int DM>
 __global__ __launch_bounds__(kWave) void bp_small_kernel(DevGraph g, BpLaunch a) {
@@ -30,38 +78,140 @@ __global__ __launch_bounds__(kWave) void bp_small_kernel(DevGraph g, BpLaunch a)
     using CWord = const __attribute__((address_space(4))) uint32_t;
     const uint32_t lane = threadIdx.x, lane4 = lane * 4u;
     const uint32_t post0 = (g.E + 1u) * 256u;  // posteriors [v][lane] after the messages
-    const uint32_t groups = (a.n_shots + kWave - 1) / kWave, n_items = groups * g.L;
     const float lim = (float)g.clamp;
     const float* lamv = reinterpret_cast<const float*>(g.lam);
-    for (;;) {
-        const uint32_t item = wave_ticket(a.counter, 1u);
-        if (item >= n_items) break;
-        const uint32_t mem = item / groups, shot = (item % groups) * kWave + lane;
-        const bool act = shot < a.n_shots;
-        uint64_t s = 0;
-        if (act) {
-            const uint8_t* sp = a.syndromes + (size_t)(a.shot0 + shot) * g.m;
-            for (uint32_t c = 0; c < g.m; c++) s |= (uint64_t)(sp[c] != 0 ? 1u : 0u) << c;
+    CWord* lam_e = (CWord*)(g.ssched + (size_t)g.L * g.scols * CWD);
+    // fewer than M other members never stop one
+    const bool limited = a.use_M && g.M < g.L;
+    *lds_at(g.E * 256u + lane4) = g.ident32;
+    // The wavefront's member, or members where there are fewer wavefronts, and
+    // its share of the shots: those of a member are split evenly over the
+    // member's wavefronts.  (Shots taken from a counter as lanes fall idle left
+    // some wavefronts with none and others with a second run to the limit.)
+    const uint32_t G = gridDim.x, b = blockIdx.x;
+    uint32_t mem = uni((uint32_t)((uint64_t)b * g.L / G));
+    const uint32_t end = max(mem + 1, uni((uint32_t)(((uint64_t)b + 1) * g.L / G)));
+    for (; mem < end; mem++) {
+        uint32_t next = 0, last = a.n_shots;
+        if (G > g.L) {
+            const uint32_t b0 = uni((uint32_t)(((uint64_t)mem * G + g.L - 1) / g.L));
+            const uint32_t b1 = uni((uint32_t)((((uint64_t)mem + 1) * G + g.L - 1) / g.L));
+            next = uni((uint32_t)((uint64_t)a.n_shots * (b - b0) / (b1 - b0)));
+            last = uni((uint32_t)((uint64_t)a.n_shots * (b - b0 + 1) / (b1 - b0)));
         }
         CWord* cols = (CWord*)(g.ssched + (size_t)mem * g.scols * CWD);
-        for (uint32_t q = 0; q < g.scols; q++) {
-            CWord* w = cols + (size_t)q * CWD;
-            const uint32_t deg = w[0] >> 8, lam = w[1];
-#pragma unroll
-            for (int j = 0; j < DM; j++)
-                if ((uint32_t)j < deg) *lds_at((w[2 + j * EW] & 0xffffu) + lane4) = lam;
-        }
-        *lds_at(g.E * 256u + lane4) = g.ident32;
-        // a zero syndrome with every lambda > 0 converges at once to e = 0
-        const bool quick = s == 0 && a.fast_zero && g.all_lam_positive;
-        uint32_t conv_t = quick ? 1u : 0u;
-        uint64_t e_conv = 0;
-        bool sat = false;
-        float satm = 0.0f;
-        uint64_t alive = __ballot(act && !quick);
-        for (uint32_t t = 1; t <= a.T_run && alive; t++) {
+        const uint64_t lower = (1ull << mem) - 1ull, own = 1ull << mem;
+        // the 64 shots taken last, one a lane: their syndromes, and those not
+        // yet started
+        uint32_t block = 0;
+        uint64_t bsynd = 0, avail = 0;
+        uint64_t busy = 0;  // lanes with a shot in work
+        uint64_t fin = 0;   // lanes whose shot is decided, its outputs to be written
+        // of the lane's shot: its index, syndrome, iteration and saturation
+        // witness; when decided: whether it converged, its decisions, and
+        // whether it ran to the limit
+        uint32_t shot = 0, t = 1;
+        uint64_t s = 0, e_conv = 0;
+        float satm = 0.0f, satf = 0.0f;
+        bool conv = false, ran_out = false;
+        for (uint32_t step = 0;; step++) {
+            while (__popcll(~busy) >= kSmallRefill) {
+                if (!avail && next < last) {
+                    block = next;
+                    next = min(next + (uint32_t)kWave, last);
+                    bool start = lane < next - block;
+                    if (start) {
+                        const uint32_t sh = block + lane, rec = sh * g.L + mem;
+                        uint64_t* cmask = a.conv_mask + (size_t)sh * (kMaxT + 1);
+                        const uint64_t at_1 = limited ? load_mask(&cmask[1]) : 0ull;
+                        bsynd = syndrome_bits(a.syndromes + (size_t)(a.shot0 + sh) * g.m, g.m);
+                        if (limited && (uint32_t)__popcll(at_1 & lower) >= g.M) {
+                            a.t_conv[rec] = 0;
+                            start = false;
+                        } else if (bsynd == 0 && a.fast_zero && g.all_lam_positive) {
+                            // converges at once to e = 0
+                            a.t_conv[rec] = 1;
+                            a.cand[rec] = 0;
+                            a.weight[rec] = 0.0;
+                            atomicAdd(&a.iters[sh], 1u);
+                            atomicOr(reinterpret_cast<unsigned long long*>(&cmask[1]), own);
+                            start = false;
+                        }
+                    }
+                    avail = __ballot(start);
+                    if (!avail) continue;
+                }
+                // (with no more shots to come, once for all lanes)
+                if (fin && (avail || !busy)) {
+                    if ((fin >> lane) & 1ull) {
+                        const uint32_t rec = shot * g.L + mem;
+                        a.t_conv[rec] = conv ? (int32_t)t : 0;
+                        atomicAdd(&a.iters[shot], t);
+                        if (conv) {
+                            a.cand[rec] = e_conv;
+                            // W(e) = sum_v e_v lambda_v in FP64, ascending v (a
+                            // column that is 0 adds an exact zero)
+                            double W = 0.0;
+#pragma unroll 4
+                            for (uint32_t v = 0; v < g.n; v++) W += (e_conv >> v) & 1ull ? g.lam64[v] : 0.0;
+                            a.weight[rec] = W;
+                        }
+                        if (satf >= lim)
+                            atomicOr(reinterpret_cast<unsigned long long*>(a.conv_mask + (size_t)shot * (kMaxT + 1)), own);
+                        if (ran_out) {
+                            // the normalised posterior, as in finish_item;
+                            // columns without checks keep lambda.  The sum
+                            // is read only where no member has converged:
+                            // finding that out costs more than adding.
+                            auto post = [&](uint32_t v) {
+                                return (double)((g.sfree >> v) & 1ull ? lamv[v] : __uint_as_float(*lds_at(post0 + v * 256u + lane4)));
+                            };
+                            double ss = 0.0;
+                            for (uint32_t v = 0; v < g.n; v++) {
+                                const double xv = post(v), sq = xv * xv;
+                                ss += sq;
+                            }
+                            if (ss > 0.0) {
+                                const double scale = kQScale / sqrt(ss);
+                                int64_t* q = a.qfix + (size_t)shot * g.n;
+                                for (uint32_t v = 0; v < g.n; v++)
+                                    atomicAdd(reinterpret_cast<unsigned long long*>(&q[v]),
+                                              (unsigned long long)llrint(post(v) * scale));
+                            }
+                        }
+                    }
+                    fin = 0;
+                }
+                if (!avail) break;
+                // the k-th idle lane takes the k-th available shot: lane k
+                // receives that shot's place in the block, then passes it on
+                const uint32_t give = (uint32_t)__popcll(avail), rank = lane_rank(~busy);
+                const uint32_t to = (avail >> lane) & 1ull ? lane_rank(avail) : give + lane - lane_rank(avail);
+                const uint32_t kth = (uint32_t)__builtin_amdgcn_ds_permute((int)(to * 4u), (int)lane);
+                const uint32_t from = 4u * (uint32_t)__builtin_amdgcn_ds_bpermute((int)(rank * 4u), (int)kth);
+                const uint32_t s_lo = (uint32_t)__builtin_amdgcn_ds_bpermute((int)from, (int)(uint32_t)bsynd);
+                const uint32_t s_hi = (uint32_t)__builtin_amdgcn_ds_bpermute((int)from, (int)(uint32_t)(bsynd >> 32));
+                const bool start = !((busy >> lane) & 1ull) && rank < give;
+                if (start) {
+                    shot = block + from / 4u;
+                    s = (uint64_t)s_hi << 32 | s_lo;
+                    t = 1;
+                    satm = 0.0f;
+                    // the initial messages: lambda of each slot's column
+#pragma unroll 8
+                    for (uint32_t q = 0; q < g.E; q++) *lds_at(q * 256u + lane4) = lam_e[q];
+                }
+                // the first `rank` available ones are taken: those whose
+                // place among them is below the number of idle lanes
+                const uint32_t idle = (uint32_t)__popcll(~busy);
+                busy |= __ballot(start);
+                avail &= ~__ballot(((avail >> lane) & 1ull) && lane_rank(avail) < idle);
+            }
+            if (!busy) break;
+            const bool act = (busy >> lane) & 1ull, ends = act && t == a.T_run;
+            uint64_t* cmask = a.conv_mask + (size_t)shot * (kMaxT + 1);
             const float al = g.alpha_t ? (float)g.alpha_t[t - 1] : (float)g.alpha;
-            const bool want_post = t == a.T_run;
+            const bool want_post = __ballot(ends) != 0;
             uint64_t e = g.e0[0], res = s;
             for (uint32_t q = 0; q < g.scols; q++) {
                 CWord* w = cols + (size_t)q * CWD;
@@ -110,50 +260,29 @@ __global__ __launch_bounds__(kWave) void bp_small_kernel(DevGraph g, BpLaunch a)
                 const bool one = L <= 0.0f;
                 e |= one ? 1ull << v : 0ull;
                 res ^= one ? flip : 0ull;
-                if (want_post) *lds_at(post0 + v * 256u + lane4) = __float_as_uint(Prec<float>::clamp(L, lim));
+                if (want_post && ends) *lds_at(post0 + v * 256u + lane4) = __float_as_uint(Prec<float>::clamp(L, lim));
             }
-            const bool met = ((alive >> lane) & 1ull) && res == 0;
-            if (met) {
-                conv_t = t;
-                e_conv = e;
-                sat = satm >= lim;
+            const bool met = act && res == 0, out = ends && !met;
+            bool stop = false;
+            if (limited && step % 8 == 7) {
+                // M members precede this one at its next iteration
+                const bool go_on = act && !met && !ends;
+                const uint32_t at = go_on ? t : 0u;
+                stop = converged_upto(cmask, at) + (uint32_t)__popcll(load_mask(&cmask[at + 1]) & lower) >= g.M && go_on;
             }
-            alive &= ~__ballot(met);
-        }
-        if (act) {
-            if (!conv_t) sat = satm >= lim;
-            const uint32_t rec = shot * g.L + mem;
-            uint64_t* cmask = a.conv_mask + (size_t)shot * (kMaxT + 1);
-            a.t_conv[rec] = (int32_t)conv_t;
-            atomicAdd(&a.iters[shot], conv_t ? conv_t : a.T_run);
-            if (sat) atomicOr(reinterpret_cast<unsigned long long*>(&cmask[0]), 1ull << mem);
-            if (conv_t) {
-                a.cand[rec] = e_conv;
-                // W(e) = sum_v e_v lambda_v in FP64, ascending v (a column that
-                // is 0 adds an exact zero)
-                double W = 0.0;
-                for (uint32_t v = 0; v < g.n; v++) W += (e_conv >> v) & 1ull ? g.lam64[v] : 0.0;
-                a.weight[rec] = W;
-                atomicOr(reinterpret_cast<unsigned long long*>(&cmask[conv_t]), 1ull << mem);
-            } else {
-                // the normalised posterior, as in finish_item; columns without
-                // checks keep lambda
-                auto post = [&](uint32_t v) {
-                    return (double)((g.sfree >> v) & 1ull ? lamv[v] : __uint_as_float(*lds_at(post0 + v * 256u + lane4)));
-                };
-                double ss = 0.0;
-                for (uint32_t v = 0; v < g.n; v++) {
-                    const double xv = post(v), sq = xv * xv;
-                    ss += sq;
+            const uint64_t done = __ballot(met || out || stop);
+            if (done) {
+                if (met) atomicOr(reinterpret_cast<unsigned long long*>(&cmask[t]), own);
+                if ((done >> lane) & 1ull) {
+                    conv = met;
+                    e_conv = e;
+                    satf = satm;
+                    ran_out = out;
                 }
-                if (ss > 0.0) {
-                    const double scale = kQScale / sqrt(ss);
-                    int64_t* q = a.qfix + (size_t)shot * g.n;
-                    for (uint32_t v = 0; v < g.n; v++)
-                        atomicAdd(reinterpret_cast<unsigned long long*>(&q[v]), (unsigned long long)llrint(post(v) * scale));
-                }
+                busy &= ~done;
+                fin |= done;
             }
+            t += (busy >> lane) & 1ull ? 1u : 0u;
         }
-        __syncthreads();
     }
 }

@@ -598,7 +598,7 @@ extern "C" int vibe_graph_create(uint32_t m, uint32_t n, const uint32_t* h_indpt
     d.lcols = d.lorder = nullptr;
     d.lgroups = 0;
     d.scols = d.sshape = 0;
-    d.sfree = 0;
+    d.sfree = d.sitems = 0;
     d.cgroups = 0;
     d.fp64 = fp64 ? 1 : 0;
     d.flood = c.schedule == 1 ? 1 : 0;
@@ -682,6 +682,17 @@ extern "C" int vibe_graph_create(uint32_t m, uint32_t n, const uint32_t* h_indpt
             else
                 d.scols++;
         d.sshape = (uint32_t)RO << 4 | (uint32_t)DM;
+        // One lane per shot takes up to T x columns steps however few shots
+        // there are; one wavefront per item takes the items in turn, each for
+        // as long as it runs, which grows with the faults a shot has.  With
+        // x = shots x members / (T x columns^2) they meet at about x = 0.35 for
+        // 61 columns and 0.6 faults a shot (B = 20000, L = 4, T = 64: 2.27 ms
+        // and 2.21), 0.4 for 37 and 0.4 (1.28, 1.24), 0.14 for 19 and 1
+        // (0.70, 0.69), below 0.1 for 7, and at 7 faults below 0.1 for 61.
+        double faults = 0.0;
+        for (uint32_t v = 0; v < n; v++) faults += std::min(priors[v], 1.0 - priors[v]);
+        const double sq = std::max((double)d.scols * d.scols - 40.0, 0.0);
+        d.sitems = std::max<uint64_t>(72, (uint64_t)(0.8 * c.T_max * sq / (1.0 + 2.0 * faults)));
         s_sched.assign((size_t)c.L * d.scols * CWD, 0);
         uint32_t* w = s_sched.data();
         for (uint32_t i = 0; i < c.L; i++)
@@ -706,6 +717,11 @@ extern "C" int vibe_graph_create(uint32_t m, uint32_t n, const uint32_t* h_indpt
                 }
                 w += CWD;
             }
+        for (uint32_t a = 0; a < E; a++) {  // lambda of each message slot's column
+            uint32_t bits;
+            std::memcpy(&bits, &lam32[h_indices[a]], 4);
+            s_sched.push_back(bits);
+        }
     }
     // interleave the schedule fields into chunk records
     const size_t nrec = s_meta.size() / kWave;

@@ -124,6 +124,7 @@ struct DevGraph {
     uint32_t scols;               // columns with a check
     uint32_t sshape;              // others per row << 4 | edges per column that the kernel is cut for
     uint64_t sfree;               // columns without a check
+    uint64_t sitems;              // shots x members from which a decode runs it
     // compact item bodies (bp_compact.h); csched is null where the graph has none
     int compact;                  // launched with the compact item body: the most edges of a
                                   // column it sums over (6 or 8), with kCompactStream; on the
@@ -236,6 +237,7 @@ int launch_bp_small(const DevGraph& g, BpLaunch a, hipStream_t st);
 // a column: v | deg << 8, lambda, then per edge 4 words (5 others per row) or
 // 5 (7 others): its message's LDS offset | c << 16, then the offsets of the
 // row's other messages, two a word (absent: the slot that holds the clamp).
+// After all members' columns: lambda of each slot's column (E words).
 constexpr uint32_t kSmallMaxE = 160, kSmallMaxRow = 8, kSmallMaxCol = 4;
 __host__ __device__ constexpr uint32_t small_edge_words(int RO) { return RO <= 5 ? 4u : 5u; }
 __host__ __device__ constexpr uint32_t small_col_words(int RO, int DM) { return RO <= 5 && DM <= 3 ? 16u : 24u; }
