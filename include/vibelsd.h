@@ -362,7 +362,9 @@ int vibe_get_launch(const vibe_graph* g, vibe_launch_t* s);
  * the slab in LDS (where it fits), and in global memory with 1, 2 and 4
  * shots per wavefront and decisions in LDS or global memory, each at full
  * occupancy, then the best of those with the BP
- * grid at 7/8, 3/4, 5/8 and 1/2 of full; applies the fastest to the handle
+ * grid at 7/8, 3/4, 5/8 and 1/2 of full (not where the batch runs one lane
+ * per shot, which small graphs do in large batches: there neither the grid
+ * nor the place of the decisions is a choice); applies the fastest to the handle
  * and stores it in a process-wide cache keyed by the graph's shape (checks,
  * columns, edges, L, M, T, chunk and level counts, LSD order, precision,
  * schedule, device) and the batch size class (floor(log2 B)).  A graph of

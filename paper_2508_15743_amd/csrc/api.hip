@@ -161,7 +161,9 @@ int decode_chunk(vibe_graph* G, const DevGraph& g, const ChunkBufs& W, const uin
     // every item resident at once: the deeper prefetch ring pays
     b.latency = items <= (uint64_t)std::min(bp_blocks, bp_latency_grid(g, in_lds)) ? 1 : 0;
     if (timed) begin_timed(G, 0, st);
-    if ((rc = bp_small_pays(g, in_lds, n) ? launch_bp_small(g, b, st) : launch_bp(g, b, st))) return rc;
+    const bool small = bp_small_pays(g, in_lds, n);
+    if (small) b.grid = G->tune_grid;
+    if ((rc = small ? launch_bp_small(g, b, st) : launch_bp(g, b, st))) return rc;
     if (timed) end_timed(G, 0, st);
     SelectLaunch s{};
     s.n_shots = n;

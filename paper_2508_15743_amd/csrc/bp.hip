@@ -1489,7 +1489,7 @@ int launch_bp_small(const DevGraph& g, BpLaunch a, hipStream_t st) {
             // which issue as much as more would
             resident = (per_cu > 8 ? 8 : per_cu > 4 ? per_cu & ~3 : per_cu) * cus;
         }
-        grid = resident;
+        grid = a.grid > 0 ? std::min(a.grid, resident) : resident;
     }
     const uint64_t items = ((uint64_t)a.n_shots + kWave - 1) / kWave * g.L;
     void* args[] = {const_cast<DevGraph*>(&g), &a};

@@ -230,7 +230,8 @@ struct BpLaunch {
 };
 int launch_bp(const DevGraph& g, const BpLaunch& a, hipStream_t st);
 // K1 with one lane per shot: whether a decode of n shots of g (as launched)
-// runs it, and the launch (no slabs).
+// runs it, and the launch (no slabs; a.grid: the most blocks, 0 = as many as
+// pay).
 bool bp_small_pays(const DevGraph& g, bool slab_in_lds, uint64_t n);
 int launch_bp_small(const DevGraph& g, BpLaunch a, hipStream_t st);
 // Limits of the graphs it takes (with m, n <= 64), and its schedule: words of

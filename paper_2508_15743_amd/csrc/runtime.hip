@@ -655,8 +655,10 @@ extern "C" int vibe_autotune(vibe_graph* g, const uint8_t* syndromes, uint64_t B
     for (int P : {1, 2, 4})
         if (P == 1 || multi_ok(g, (uint32_t)P))
             for (int dec : {0, 1})
-                // the compact item body keeps its decisions one way only
-                if (dec == 0 || (!d.layered && !(P == 1 && compact_view(d).compact))) first.push_back(vibe_launch_t{0, 0, P, dec, 0, 0.0});
+                // the compact item body and the form with one lane per shot
+                // keep their decisions one way only
+                if (dec == 0 || (!d.layered && !(P == 1 && (compact_view(d).compact || bp_small_pays(d, false, B)))))
+                    first.push_back(vibe_launch_t{0, 0, P, dec, 0, 0.0});
     vibe_launch_t best{0, 0, 1, 0, 0, 1e30};
     bool timed = false;
     for (const vibe_launch_t& s : first) {
@@ -677,7 +679,12 @@ extern "C" int vibe_autotune(vibe_graph* g, const uint8_t* syndromes, uint64_t B
         if (best.slab_in_lds) v.dec_global = v.compact = 0;
         const int full = bp_grid(v, best.slab_in_lds != 0);
         const vibe_launch_t base = best;
+        // a smaller grid is for one wavefront per item: the form with one
+        // lane per shot sets its own, and a grid chosen on it would bind the
+        // smaller batches, which do not run it
+        const bool small = bp_small_pays(v, best.slab_in_lds != 0, B);
         for (int eighths : {7, 6, 5, 4}) {
+            if (small) break;
             vibe_launch_t s = base;
             s.grid = full * eighths / 8;
             if (s.grid < 1) continue;

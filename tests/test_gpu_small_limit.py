@@ -72,6 +72,48 @@ def test_lanes_that_take_new_shots(torch_cuda, key):
     G.close()
 
 
+def test_a_set_grid_holds(torch_cuda):
+    """Launch settings on the form with one lane per shot: a grid below the
+    member count makes wavefronts run several members; a grid of one block
+    takes longer than all of them."""
+    import paper_2508_15743_amd as P
+
+    torch = torch_cuda
+    dem = code_capacity_dem(5, 0.05)
+    G = P.Graph.from_dem(dem, permutations(dem.n, 16, 5), L=16, M=5, T_max=8)
+    s = torch.from_numpy(sample(dem, 20000, 6).syndromes).to("cuda:0")
+    want = G.decode(s)
+    ms = {}
+    for grid in (0, 33, 7, 1):
+        G.set_launch(slab_in_lds=0, grid=grid)
+        P.vibe_profile_enable(G.handle, True)
+        got = G.decode(s)
+        torch.cuda.synchronize()
+        ms[grid] = P.vibe_profile_read(G.handle)["bp_ensemble"][0]
+        assert torch.equal(got[0], want[0]) and torch.equal(got[1], want[1])
+        assert torch.equal(got[2][:, DET], want[2][:, DET])
+    print(f"BP ms by grid: {ms}", flush=True)
+    assert ms[1] > 5 * ms[0]
+    G.close()
+
+
+def test_autotune_times_no_setting_that_changes_nothing(torch_cuda):
+    """Where the batch runs one lane per shot, neither a smaller grid nor the
+    decisions' place is a choice, so none is stored."""
+    import paper_2508_15743_amd as P
+
+    torch = torch_cuda
+    dem = code_capacity_dem(5, 0.05)
+    s = torch.from_numpy(sample(dem, 4000, 6).syndromes).to("cuda:0")
+    for L in (9, 11, 13, 15):
+        G = P.Graph.from_dem(dem, permutations(dem.n, L, 5), L=L, M=3, T_max=19)
+        ch = G.autotune(s)
+        print(f"{L} members: {ch}", flush=True)
+        if ch["slab_in_lds"] == 0 and ch["shots_per_wave"] == 1:
+            assert ch["grid"] == 0 and ch["decisions_global"] <= 0
+        G.close()
+
+
 def test_members_past_the_correction_limit_stop(torch_cuda):
     """With M = 1, members that do not converge must not run to the iteration
     limit on shots that another member decides early."""
