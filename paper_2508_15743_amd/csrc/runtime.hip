@@ -843,13 +843,6 @@ BatchLayout batch_layout(vibe_graph* G, uint64_t shots, uint32_t n_req, bool com
     return L;
 }
 
-// The layout used in a pool of `pool` bytes: with compact suffix states
-// unless only the general item body's smaller slab fits the pool.
-BatchLayout batch_layout_in(size_t pool, vibe_graph* G, uint64_t shots, uint32_t n_req) {
-    BatchLayout L = batch_layout(G, shots, n_req, true);
-    return L.bytes > pool ? batch_layout(G, shots, n_req, false) : L;
-}
-
 }  // namespace
 
 struct vibe_server {
@@ -932,8 +925,7 @@ void server_loop(vibe_server* S) {
                 vibe_graph* G = S->graphs[gi];
                 const size_t room = S->map.largest();
                 // candidates within the batch limits, then the longest
-                // prefix of them whose footprint fits (it grows with the
-                // prefix, so a binary search finds it)
+                // prefix of them whose footprint fits
                 std::vector<size_t> pick;
                 std::vector<uint64_t> upto;  // shots of the first k + 1 candidates
                 uint64_t shots = 0;
@@ -945,21 +937,27 @@ void server_loop(vibe_server* S) {
                     shots += r.req.B;
                     upto.push_back(shots);
                 }
-                auto fits = [&](size_t k, BatchLayout* out) {  // the first k candidates
-                    BatchLayout t = batch_layout_in(S->pool.bytes, G, upto[k - 1], (uint32_t)k);
-                    if (out) *out = t;
-                    return t.one_round && t.bytes <= room;
+                // (it grows with the prefix, so a binary search finds it)
+                auto fits = [&](size_t k, bool compact, size_t bytes) {  // the first k candidates
+                    BatchLayout t = batch_layout(G, upto[k - 1], (uint32_t)k, compact);
+                    const bool ok = t.one_round && t.bytes <= bytes;
+                    if (ok) lay = t;
+                    return ok;
                 };
                 size_t lo = 0, hi = pick.size();  // fits(lo) (or lo = 0), !fits(hi + 1)
                 while (lo < hi) {
                     const size_t mid = (lo + hi + 1) / 2;
-                    if (fits(mid, nullptr))
+                    if (fits(mid, false, room))
                         lo = mid;
                     else
                         hi = mid - 1;
                 }
                 pick.resize(lo);
-                if (lo) fits(lo, &lay);
+                // With compact suffix states and every LSD block that resides
+                // the footprint is another: taken where it is no larger, or
+                // within a slot's share of the pool.  Beyond that it would
+                // keep out batches that the pool holds beside this one.
+                if (lo) (void)fits(lo, true, std::max(lay.bytes, std::min(room, S->pool.bytes / S->slots.size())));
                 if (pick.empty() && !any_busy) {
                     // cannot happen for admitted requests (each fits the
                     // whole pool alone), kept as a guard against a stall
