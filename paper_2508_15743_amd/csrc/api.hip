@@ -387,7 +387,7 @@ extern "C" int vibe_bp_ensemble(vibe_graph* G, const uint8_t* syndromes, uint64_
     if (!B) return VIBE_OK;
     hipStream_t st = static_cast<hipStream_t>(stream);
     const bool in_lds = bp_slab_fits_lds(G->h.dg);
-    const DevGraph g = in_lds ? G->h.dg : compact_view(G->h.dg);
+    const DevGraph g = in_lds ? G->h.dg : compact_choice(G->h.dg, std::min<uint64_t>(B, UINT32_MAX) * G->h.dg.L);
     const uint32_t bc = chunk_for(g, B, false);
     const int bpg = bp_grid(g, in_lds);
     ChunkBufs W;

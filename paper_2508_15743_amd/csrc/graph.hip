@@ -151,6 +151,25 @@ DevGraph compact_view(DevGraph d) {
     return d;
 }
 
+// The compact bodies keep two or four words per check in LDS, the general one
+// one, so on graphs of thousands of checks fewer of them reside.  One runs an
+// item in about 0.62 of the other's time where few reside, and neither gains
+// from more than 16 wavefronts per CU.  Rows of 2.5 edges, m = n = 3000, 8
+// members (general: 13 wavefronts per CU), parallel schedule (3): 40 shots
+// 0.11 ms against 0.19, 600 0.48 against 0.42, 3000 1.96 against 1.19; one
+// member, 3000 shots (four times what resides) 0.36 against 0.41; serial (6):
+// 40 shots 0.12 against 0.18, 600 0.34 against 0.34, 3000 1.15 against 1.01.
+DevGraph compact_choice(const DevGraph& d, uint64_t items) {
+    const DevGraph c = compact_view(d);
+    if (!c.compact || c.layered) return c;
+    const int resident = bp_grid(c, false);
+    if (items <= 4ull * resident) return c;
+    DevGraph a = d;
+    a.dec_global = dec_global_pays(d) ? 1 : 0;
+    const int enough = bp_grid_for(false, c.flood != 0, false, 0, false, false, 1, false, false, c.compact);
+    return resident >= 0.6 * std::min(bp_grid(a, false), enough) ? c : d;
+}
+
 DevGraph decode_view(const vibe_graph* G, bool allow_multi, uint64_t shots, bool allow_compact) {
     DevGraph d = G->h.dg;
     const uint32_t P = G->tune_P;
@@ -160,7 +179,7 @@ DevGraph decode_view(const vibe_graph* G, bool allow_multi, uint64_t shots, bool
         d.max_chunks = G->multi_max_chunks[P / 4];
         d.P = P;
     }
-    if (allow_compact) d = compact_view(d);
+    if (allow_compact) d = compact_choice(d, shots == UINT64_MAX ? shots : bp_items(d, shots));
     if (!d.layered && !d.compact) {
         if (G->tune_dec >= 0) {
             d.dec_global = G->tune_dec;

@@ -328,6 +328,8 @@ DevGraph decode_view(const vibe_graph* G, bool allow_multi = true, uint64_t shot
 // d with the compact item body switched on where the graph has its data and
 // runs one shot per wavefront.
 DevGraph compact_view(DevGraph d);
+// d, or that where it is the faster for so many work items.
+DevGraph compact_choice(const DevGraph& d, uint64_t items);
 // Whether decisions in global memory let more BP wavefronts reside than a
 // decision bitmap in LDS (g.dec_global ignored).
 bool dec_global_pays(const DevGraph& g);

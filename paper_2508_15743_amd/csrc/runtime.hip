@@ -657,7 +657,7 @@ extern "C" int vibe_autotune(vibe_graph* g, const uint8_t* syndromes, uint64_t B
             for (int dec : {0, 1})
                 // the compact item body and the form with one lane per shot
                 // keep their decisions one way only
-                if (dec == 0 || (!d.layered && !(P == 1 && (compact_view(d).compact || bp_small_pays(d, false, B)))))
+                if (dec == 0 || (!d.layered && !(P == 1 && (compact_choice(d, bp_items(d, B)).compact || bp_small_pays(d, false, B)))))
                     first.push_back(vibe_launch_t{0, 0, P, dec, 0, 0.0});
     vibe_launch_t best{0, 0, 1, 0, 0, 1e30};
     bool timed = false;
