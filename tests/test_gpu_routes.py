@@ -44,6 +44,32 @@ def _ms(torch, call, reps=5):
     return best * 1e3, out
 
 
+def test_ragged_round_of_mostly_general_work(torch_cuda):
+    """A few shots of a graph with compact data beside many of one without
+    (columns of up to 15 checks): no longer than the two apart."""
+    import paper_2508_15743_amd as P
+
+    torch = torch_cuda
+    pairs = []
+    for dem, B in ((_random(200, 4000, 8, 15, 2), 1200), (circuit_dem(3, 3, 1e-3), 10)):
+        G = P.Graph.from_dem(dem, permutations(dem.n, 16, 1), L=16, M=5, T_max=12)
+        pairs.append((G, torch.from_numpy(sample(dem, B, 3).syndromes).to("cuda:0")))
+    rt = P.Runtime()
+    apart, want = _ms(torch, lambda: [rt.decode([p])[0] for p in pairs], 3)
+    ms, got = _ms(torch, lambda: rt.decode(pairs), 3)
+    print(f"one round {ms:.2f} ms, two calls {apart:.2f} ms", flush=True)
+    for a, b in zip(got, want):
+        assert torch.equal(a[0], b[0]) and torch.equal(a[1], b[1]) and torch.equal(a[2][:, DET], b[2][:, DET])
+    assert ms <= 1.06 * apart
+    # more compact work than that: the compact launch runs the other's items too
+    few = [(pairs[0][0], pairs[0][1][:7].contiguous()), (pairs[1][0], pairs[1][1].repeat(300, 1))]
+    for a, b in zip(rt.decode(few), [rt.decode([p])[0] for p in few]):
+        assert torch.equal(a[0], b[0]) and torch.equal(a[1], b[1]) and torch.equal(a[2][:, DET], b[2][:, DET])
+    rt.close()
+    for G, _ in pairs:
+        G.close()
+
+
 def test_thousands_of_checks_with_short_rows(torch_cuda):
     """The compact bodies' row states let few wavefronts reside on 3000 checks;
     a ragged round on the parallel schedule runs the general body."""
