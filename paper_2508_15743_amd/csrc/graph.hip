@@ -1,10 +1,12 @@
 // Offline stage (paper Sec. III.D.1): validate the detector error model, derive
 // the channel LLRs, build the member schedules and upload everything once.
 #include <algorithm>
+#include <atomic>
 #include <cmath>
 #include <cstring>
 #include <mutex>
 #include <queue>
+#include <thread>
 
 #include "internal.h"
 
@@ -39,6 +41,57 @@ int upload(GraphHost& h, const T* src, size_t count, const T** dst) {
     }
     *dst = static_cast<const T*>(p);
     return VIBE_OK;
+}
+
+// One member's schedule: its chunk records, and its part of the compact item
+// body's data.
+struct MemberSched {
+    std::vector<unsigned char> recs;
+    std::vector<uint32_t> csched, crec0, row0, row2;
+    uint32_t levels = 0, chunks = 0, groups = 0, dense0 = 0;
+    uint64_t kept = 0;  // chunks whose records are expected to fit
+    bool whole = true;  // every column is placed
+};
+
+// What building one needs besides, reused from member to member.  Per chunk
+// slot (64 a chunk): the meta word, the column, its channel LLR and the
+// initial suffix state.
+struct SchedScratch {
+    std::vector<uint32_t> meta, v, init32;
+    std::vector<float> lam32;
+    std::vector<double> lam64;
+    std::vector<uint64_t> init64;
+    std::vector<uint32_t> last, level, height, npred, pos, succ, taken, running32, later;
+    std::vector<uint64_t> skipped, running64;
+    std::vector<float> expected;
+};
+
+// fn(i, scratch) for i < count, in any order, on up to eight threads where
+// `work` (edges x members) is worth starting them, which takes 0.15 ms: 2^13
+// take 1 to 4 ms on one.
+// Returns false if memory ran out.
+template <class Scratch, class F>
+bool for_members(uint32_t count, uint64_t work, F&& fn) {
+    std::atomic<uint32_t> next{0};
+    std::atomic<bool> ok{true};
+    auto run = [&]() {
+        try {
+            Scratch scratch;
+            for (uint32_t i; ok && (i = next.fetch_add(1)) < count;) fn(i, scratch);
+        } catch (...) {
+            ok = false;
+        }
+    };
+    std::vector<std::thread> helpers;
+    uint32_t n = work < (1u << 13) ? 1u : std::min(8u, std::max(1u, std::thread::hardware_concurrency()));
+    n = std::min(n, count);
+    try {
+        while (helpers.size() + 1 < n) helpers.emplace_back(run);
+    } catch (...) {  // as many as could be started
+    }
+    run();
+    for (std::thread& t : helpers) t.join();
+    return ok;
 }
 
 void free_all(GraphHost& h) {
@@ -346,237 +399,255 @@ extern "C" int vibe_graph_create(uint32_t m, uint32_t n, const uint32_t* h_indpt
     //      chain of successors below them, then by permutation position) into
     //      at most 64 edges each, which reaches max(#levels, ceil(E / 64))
     //      chunks on the workloads here.
-    std::vector<uint32_t> s_meta, s_v, init32;
-    std::vector<float> s_lam32;
-    std::vector<double> s_lam64;
-    std::vector<uint64_t> init64;
     // compact item bodies (bp_compact.h): FP32, serial or parallel schedule,
-    // columns of at most 8 checks
-    const bool want_compact = !fp64 && !layered && max_col <= 8 && E && m < 8192;
-    std::vector<uint32_t> c_sched, c_rec0, c_row0, c_row2, c_group(c.L + 1, 0), c_dense0(c.L, 0), c_later(m);
-    std::vector<float> c_exp;
-    uint64_t c_chunks = 0;
-    std::vector<uint32_t> member_chunk(c.L + 1, 0);
-    uint32_t lev_min = UINT32_MAX, lev_max = 0, ch_min = UINT32_MAX, ch_max = 0;
-    {
-        const uint32_t kNone = UINT32_MAX;
-        std::vector<uint32_t> last(m), level(n), height(n), npred(n), pos(n), succ(E);
-        std::vector<uint32_t> taken;
-        std::vector<uint64_t> skipped;
-        std::vector<uint32_t> running32(m);
-        std::vector<uint64_t> running64(m);
+    // columns of at most 8 checks, row states within 64 KB of LDS
+    DevGraph dc{};
+    dc.m = m;
+    dc.words_m = words_m;
+    dc.words_n = words_n;
+    dc.flood = c.schedule == 1 ? 1 : 0;
+    dc.compact = 1;
+    const bool want_compact =
+        !fp64 && !layered && max_col <= 8 && E && m < 8192 && bp_lds_bytes(dc, false) <= 64 * 1024;
+    const uint32_t kNone = UINT32_MAX;
+    const uint32_t rb = rec_bytes(fp64), ri0 = rec_init(fp64), fb = fp64 ? 8u : 4u;
+    auto member = [&](uint32_t i, SchedScratch& w, MemberSched& o) {
+        std::vector<uint32_t>&s_meta = w.meta, &s_v = w.v, &init32 = w.init32, &c_sched = o.csched, &c_rec0 = o.crec0;
+        std::vector<float>& s_lam32 = w.lam32;
+        std::vector<double>& s_lam64 = w.lam64;
+        std::vector<uint64_t>& init64 = w.init64;
+        std::vector<uint32_t>&last = w.last, &level = w.level, &height = w.height, &npred = w.npred, &pos = w.pos;
+        std::vector<uint32_t>&succ = w.succ, &taken = w.taken, &running32 = w.running32, &c_later = w.later;
+        std::vector<uint64_t>&skipped = w.skipped, &running64 = w.running64;
+        std::vector<float>& c_exp = w.expected;
+        last.resize(m), running32.resize(m), running64.resize(m), c_later.resize(m);
+        level.resize(n), height.resize(n), npred.resize(n), pos.resize(n), succ.resize(E);
+        s_meta.clear(), s_v.clear(), s_lam32.clear(), s_lam64.clear();
         size_t nchunks = 0;
-        for (uint32_t i = 0; i < (layered ? 0u : c.L); i++) {  // the layered schedule has no chunks
-            const uint32_t* pi = perms + (size_t)i * n;
-            std::fill(last.begin(), last.end(), kNone);
-            std::fill(succ.begin(), succ.end(), kNone);
-            uint32_t nlev = 0, ncols = 0;
-            for (uint32_t a = 0; a < n; a++) {
-                const uint32_t v = pi[a];
-                pos[v] = a;
-                npred[v] = 0;
-                uint32_t lv = 0;
-                for (uint32_t j = cp[v]; j < cp[v + 1]; j++) {
-                    const uint32_t r = ci[j], u = last[r];
-                    if (u != kNone) {
-                        // arc u -> v through row r; u's edge on r is the one
-                        // whose check is r
-                        uint32_t ju = cp[u];
-                        while (ci[ju] != r) ju++;
-                        succ[ju] = v;
-                        bool dup = false;
-                        for (uint32_t j2 = cp[v]; j2 < j; j2++) dup |= last[ci[j2]] == u;
-                        if (!dup) npred[v]++;
-                        lv = std::max(lv, level[u]);
-                    }
-                }
-                for (uint32_t j = cp[v]; j < cp[v + 1]; j++) last[ci[j]] = v;
-                level[v] = lv + 1;
-                if (cp[v + 1] > cp[v]) {
-                    nlev = std::max(nlev, level[v]);
-                    ncols++;
+        const uint32_t* pi = perms + (size_t)i * n;
+        std::fill(last.begin(), last.end(), kNone);
+        std::fill(succ.begin(), succ.end(), kNone);
+        uint32_t nlev = 0, ncols = 0;
+        for (uint32_t a = 0; a < n; a++) {
+            const uint32_t v = pi[a];
+            pos[v] = a;
+            npred[v] = 0;
+            uint32_t lv = 0;
+            for (uint32_t j = cp[v]; j < cp[v + 1]; j++) {
+                const uint32_t r = ci[j], u = last[r];
+                if (u != kNone) {
+                    // arc u -> v through row r; u's edge on r is the one
+                    // whose check is r
+                    uint32_t ju = cp[u];
+                    while (ci[ju] != r) ju++;
+                    succ[ju] = v;
+                    bool dup = false;
+                    for (uint32_t j2 = cp[v]; j2 < j; j2++) dup |= last[ci[j2]] == u;
+                    if (!dup) npred[v]++;
+                    lv = std::max(lv, level[u]);
                 }
             }
-            for (uint32_t a = n; a-- > 0;) {
-                const uint32_t u = pi[a];
-                uint32_t h = 0;
-                for (uint32_t j = cp[u]; j < cp[u + 1]; j++)
-                    if (succ[j] != kNone) h = std::max(h, height[succ[j]]);
-                height[u] = h + 1;
+            for (uint32_t j = cp[v]; j < cp[v + 1]; j++) last[ci[j]] = v;
+            level[v] = lv + 1;
+            if (cp[v + 1] > cp[v]) {
+                nlev = std::max(nlev, level[v]);
+                ncols++;
             }
-            lev_min = std::min(lev_min, nlev);
-            lev_max = std::max(lev_max, nlev);
-            // ready queue keyed by (larger height, earlier position)
-            auto key = [&](uint32_t v) { return ((uint64_t)(~height[v]) << 32) | pos[v]; };
-            std::priority_queue<uint64_t, std::vector<uint64_t>, std::greater<uint64_t>> ready;
-            for (uint32_t a = 0; a < n; a++) {
-                const uint32_t v = pi[a];
-                if (cp[v + 1] > cp[v] && npred[v] == 0) ready.push(key(v));
-            }
-            member_chunk[i] = (uint32_t)nchunks;
-            const size_t first_slot = nchunks * kWave;
-            uint32_t placed = 0;
-            while (!ready.empty()) {
-                uint32_t cap = kWave, dmax = 0;
-                taken.clear();
-                skipped.clear();
-                while (!ready.empty() && cap > 0 && skipped.size() < (size_t)kWave) {
-                    const uint64_t kv = ready.top();
-                    ready.pop();
-                    const uint32_t v = pi[(uint32_t)kv];
-                    const uint32_t d = cp[v + 1] - cp[v];
-                    if (d <= cap) {
-                        taken.push_back(v);
-                        cap -= d;
-                        dmax = std::max(dmax, d);
-                    } else {
-                        skipped.push_back(kv);
-                    }
-                }
-                for (uint64_t kv : skipped) ready.push(kv);
-                for (uint32_t v : taken) {
-                    const uint32_t d = cp[v + 1] - cp[v];
-                    for (uint32_t j = 0; j < d; j++) {
-                        s_meta.push_back(ci[cp[v] + j] | (j << 16) | (d << kMetaDegShift) | (dmax << kMetaDmaxShift));
-                        s_v.push_back(v);
-                        if (fp64) s_lam64.push_back(lam64[v]);
-                        else s_lam32.push_back(lam32[v]);
-                    }
-                }
-                for (uint32_t q = kWave - cap; q < (uint32_t)kWave; q++) {  // unused slots
-                    s_meta.push_back(dmax << kMetaDmaxShift);
-                    s_v.push_back(0);
-                    if (fp64) s_lam64.push_back(0.0);
-                    else s_lam32.push_back(0.0f);
-                }
-                nchunks++;
-                placed += (uint32_t)taken.size();
-                // successors become ready once this chunk is complete
-                for (uint32_t u : taken)
-                    for (uint32_t j = cp[u]; j < cp[u + 1]; j++) {
-                        const uint32_t v = succ[j];
-                        if (v == kNone) continue;
-                        bool dup = false;
-                        for (uint32_t j2 = cp[u]; j2 < j; j2++) dup |= succ[j2] == v;
-                        if (!dup && --npred[v] == 0) ready.push(key(v));
-                    }
-            }
-            if (placed != ncols) return fail(VIBE_EINVAL, "internal: schedule does not cover every column");
-            const uint32_t nch = (uint32_t)(nchunks - member_chunk[i]);
-            ch_min = std::min(ch_min, nch);
-            ch_max = std::max(ch_max, nch);
-            // suffix states of the initial messages mu = lambda, from the end
-            // of the sweep backwards
-            const size_t end_slot = nchunks * kWave;
-            if (fp64) {
-                init64.resize(end_slot);
-                std::fill(running64.begin(), running64.end(), ident64);
-                for (size_t q = end_slot; q-- > first_slot;) {
-                    if (!((s_meta[q] >> kMetaDegShift) & 15u)) {
-                        init64[q] = ident64;
-                        continue;
-                    }
-                    const uint32_t r = s_meta[q] & 0xffffu;
-                    init64[q] = running64[r];
-                    running64[r] = rs_combine<uint64_t>(enc64(lam64[s_v[q]]), running64[r]);
-                }
-            } else {
-                init32.resize(end_slot);
-                std::fill(running32.begin(), running32.end(), ident32);
-                for (size_t q = end_slot; q-- > first_slot;) {
-                    if (!((s_meta[q] >> kMetaDegShift) & 15u)) {
-                        init32[q] = ident32;
-                        continue;
-                    }
-                    const uint32_t r = s_meta[q] & 0xffffu;
-                    init32[q] = running32[r];
-                    running32[r] = rs_combine<uint32_t>(enc32(lam32[s_v[q]]), running32[r]);
-                }
-                if (want_compact) {
-                    // the compact schedule; the record of the initial
-                    // messages of every chunk; and how many records a chunk
-                    // is expected to hold: an edge with r later ones in its
-                    // row is the least of them with probability 1 / (r + 1)
-                    // (groups of four chunks, an even number of them)
-                    const uint32_t ng = (nch + 7) / 8 * 2;
-                    c_group[i + 1] = c_group[i] + ng;
-                    c_sched.resize((size_t)c_group[i + 1] * 512);
-                    c_rec0.resize((size_t)c_group[i + 1] * 64, 0);
-                    c_exp.assign(nch, 0.0f);
-                    std::fill(c_later.begin(), c_later.end(), 0u);
-                    for (uint32_t k = ng * 4; k-- > 0;) {
-                        const size_t at = (size_t)(member_chunk[i] + k) * kWave;
-                        uint32_t* sc = &c_sched[(size_t)(c_group[i] + k / 4) * 512];
-                        uint32_t* rc = &c_rec0[((size_t)c_group[i] * 4 + k) * 16];
-                        uint32_t vals = 0;
-                        for (uint32_t q = 0; q < (uint32_t)kWave; q++) {
-                            const uint32_t mw = k < nch ? s_meta[at + q] : 0u, deg = (mw >> kMetaDegShift) & 15u;
-                            const uint32_t seg = (mw >> 16) & 15u, r = mw & 0xffffu;
-                            uint32_t& meta = sc[q * 4 + k % 4];
-                            if (!deg) {
-                                meta = m << 18 | q << 2;
-                                continue;
-                            }
-                            std::memcpy(&sc[256 + q * 4 + k % 4], &s_lam32[at + q], 4);
-                            meta = (seg + 1 == deg ? 1u << 31 : 0u) | r << 18 |
-                                   (((1u << deg) - 1u) & ~(1u << seg)) << 8 | (q - seg) << 2;
-                            const uint32_t bits = enc32(s_lam32[at + q]), mag = init32[at + q] & 0x7fffffffu;
-                            if (bits >> 31) rc[q / 32] |= 1u << (q % 32);
-                            if ((bits & 0x7fffffffu) < mag) {
-                                if (vals < 12) rc[4 + vals] = mag;
-                                vals++;
-                                rc[2 + q / 32] |= 1u << (q % 32);
-                            }
-                            c_exp[k] += 1.0f / (float)(++c_later[r]);
-                        }
-                        if (vals > 12) rc[2] = rc[3] = 0xffffffffu;
-                    }
-                    if (i == 0) {
-                        c_row0 = running32;
-                        if (c.schedule == 1) {  // the rows' next least magnitudes
-                            c_row2.assign(m, ident32);
-                            std::vector<uint32_t> least(m, ident32);
-                            for (size_t q = first_slot; q < end_slot; q++) {
-                                if (!((s_meta[q] >> kMetaDegShift) & 15u)) continue;
-                                const uint32_t r = s_meta[q] & 0xffffu, mag = enc32(s_lam32[q]) & 0x7fffffffu;
-                                c_row2[r] = std::min(c_row2[r], std::max(least[r], mag));
-                                least[r] = std::min(least[r], mag);
-                            }
-                        }
-                    }
-                    // the first group that keeps its states in the slab
-                    // slots: least bytes over the sweep, 64 for a record that
-                    // fits, 256 for states in the slots, and for a record
-                    // that may not fit (expected count plus 2.5 standard
-                    // deviations above 12) what the late load costs
-                    uint32_t kd = nch;
-                    double cost = 0.0, best = 0.0;
-                    for (uint32_t k = nch; k-- > 0;) {
-                        const double ex = c_exp[k];
-                        cost += 256.0 - (ex + 2.5 * std::sqrt(ex) <= 12.0 ? 64.0 : 1024.0);
-                        if (k % 8 == 0 && cost < best) {
-                            best = cost;
-                            kd = k;
-                        }
-                    }
-                    c_dense0[i] = kd == nch ? ng : kd / 4;
-                    c_chunks += kd;
-                }
-            }
-            if (nchunks * kWave >= (1ull << 32)) return fail(VIBE_EUNSUPPORTED, "schedules exceed 2^32 slots");
         }
-        member_chunk[c.L] = (uint32_t)nchunks;
-        if (nchunks == 0) {  // no edges at all: keep one (unused) record
-            s_meta.assign(kWave, 0);
-            s_v.assign(kWave, 0);
-            s_lam32.assign(kWave, 0.0f);
-            s_lam64.assign(kWave, 0.0);
-            init32.assign(kWave, ident32);
-            init64.assign(kWave, ident64);
+        for (uint32_t a = n; a-- > 0;) {
+            const uint32_t u = pi[a];
+            uint32_t h = 0;
+            for (uint32_t j = cp[u]; j < cp[u + 1]; j++)
+                if (succ[j] != kNone) h = std::max(h, height[succ[j]]);
+            height[u] = h + 1;
         }
-        if (ch_min == UINT32_MAX) ch_min = 0;
+        o.levels = nlev;
+        // ready queue keyed by (larger height, earlier position)
+        auto key = [&](uint32_t v) { return ((uint64_t)(~height[v]) << 32) | pos[v]; };
+        std::priority_queue<uint64_t, std::vector<uint64_t>, std::greater<uint64_t>> ready;
+        for (uint32_t a = 0; a < n; a++) {
+            const uint32_t v = pi[a];
+            if (cp[v + 1] > cp[v] && npred[v] == 0) ready.push(key(v));
+        }
+        uint32_t placed = 0;
+        while (!ready.empty()) {
+            uint32_t cap = kWave, dmax = 0;
+            taken.clear();
+            skipped.clear();
+            while (!ready.empty() && cap > 0 && skipped.size() < (size_t)kWave) {
+                const uint64_t kv = ready.top();
+                ready.pop();
+                const uint32_t v = pi[(uint32_t)kv];
+                const uint32_t d = cp[v + 1] - cp[v];
+                if (d <= cap) {
+                    taken.push_back(v);
+                    cap -= d;
+                    dmax = std::max(dmax, d);
+                } else {
+                    skipped.push_back(kv);
+                }
+            }
+            for (uint64_t kv : skipped) ready.push(kv);
+            for (uint32_t v : taken) {
+                const uint32_t d = cp[v + 1] - cp[v];
+                for (uint32_t j = 0; j < d; j++) {
+                    s_meta.push_back(ci[cp[v] + j] | (j << 16) | (d << kMetaDegShift) | (dmax << kMetaDmaxShift));
+                    s_v.push_back(v);
+                    if (fp64) s_lam64.push_back(lam64[v]);
+                    else s_lam32.push_back(lam32[v]);
+                }
+            }
+            for (uint32_t q = kWave - cap; q < (uint32_t)kWave; q++) {  // unused slots
+                s_meta.push_back(dmax << kMetaDmaxShift);
+                s_v.push_back(0);
+                if (fp64) s_lam64.push_back(0.0);
+                else s_lam32.push_back(0.0f);
+            }
+            nchunks++;
+            placed += (uint32_t)taken.size();
+            // successors become ready once this chunk is complete
+            for (uint32_t u : taken)
+                for (uint32_t j = cp[u]; j < cp[u + 1]; j++) {
+                    const uint32_t v = succ[j];
+                    if (v == kNone) continue;
+                    bool dup = false;
+                    for (uint32_t j2 = cp[u]; j2 < j; j2++) dup |= succ[j2] == v;
+                    if (!dup && --npred[v] == 0) ready.push(key(v));
+                }
+        }
+        o.whole = placed == ncols;
+        const uint32_t nch = (uint32_t)nchunks;
+        o.chunks = nch;
+        // suffix states of the initial messages mu = lambda, from the end
+        // of the sweep backwards
+        const size_t end_slot = nchunks * kWave;
+        if (fp64) {
+            init64.resize(end_slot);
+            std::fill(running64.begin(), running64.end(), ident64);
+            for (size_t q = end_slot; q-- > 0;) {
+                if (!((s_meta[q] >> kMetaDegShift) & 15u)) {
+                    init64[q] = ident64;
+                    continue;
+                }
+                const uint32_t r = s_meta[q] & 0xffffu;
+                init64[q] = running64[r];
+                running64[r] = rs_combine<uint64_t>(enc64(lam64[s_v[q]]), running64[r]);
+            }
+        } else {
+            init32.resize(end_slot);
+            std::fill(running32.begin(), running32.end(), ident32);
+            for (size_t q = end_slot; q-- > 0;) {
+                if (!((s_meta[q] >> kMetaDegShift) & 15u)) {
+                    init32[q] = ident32;
+                    continue;
+                }
+                const uint32_t r = s_meta[q] & 0xffffu;
+                init32[q] = running32[r];
+                running32[r] = rs_combine<uint32_t>(enc32(lam32[s_v[q]]), running32[r]);
+            }
+            if (want_compact) {
+                // the compact schedule; the record of the initial
+                // messages of every chunk; and how many records a chunk
+                // is expected to hold: an edge with r later ones in its
+                // row is the least of them with probability 1 / (r + 1)
+                // (groups of four chunks, an even number of them)
+                const uint32_t ng = (nch + 7) / 8 * 2;
+                o.groups = ng;
+                c_sched.assign((size_t)ng * 512, 0u);
+                c_rec0.assign((size_t)ng * 64, 0u);
+                c_exp.assign(nch, 0.0f);
+                std::fill(c_later.begin(), c_later.end(), 0u);
+                for (uint32_t k = ng * 4; k-- > 0;) {
+                    const size_t at = (size_t)k * kWave;
+                    uint32_t* sc = &c_sched[(size_t)(k / 4) * 512];
+                    uint32_t* rc = &c_rec0[(size_t)k * 16];
+                    uint32_t vals = 0;
+                    for (uint32_t q = 0; q < (uint32_t)kWave; q++) {
+                        const uint32_t mw = k < nch ? s_meta[at + q] : 0u, deg = (mw >> kMetaDegShift) & 15u;
+                        const uint32_t seg = (mw >> 16) & 15u, r = mw & 0xffffu;
+                        uint32_t& meta = sc[q * 4 + k % 4];
+                        if (!deg) {
+                            meta = m << 18 | q << 2;
+                            continue;
+                        }
+                        std::memcpy(&sc[256 + q * 4 + k % 4], &s_lam32[at + q], 4);
+                        meta = (seg + 1 == deg ? 1u << 31 : 0u) | r << 18 |
+                               (((1u << deg) - 1u) & ~(1u << seg)) << 8 | (q - seg) << 2;
+                        const uint32_t bits = enc32(s_lam32[at + q]), mag = init32[at + q] & 0x7fffffffu;
+                        if (bits >> 31) rc[q / 32] |= 1u << (q % 32);
+                        if ((bits & 0x7fffffffu) < mag) {
+                            if (vals < 12) rc[4 + vals] = mag;
+                            vals++;
+                            rc[2 + q / 32] |= 1u << (q % 32);
+                        }
+                        c_exp[k] += 1.0f / (float)(++c_later[r]);
+                    }
+                    if (vals > 12) rc[2] = rc[3] = 0xffffffffu;
+                }
+                if (i == 0) {
+                    o.row0 = running32;
+                    if (c.schedule == 1) {  // the rows' next least magnitudes
+                        o.row2.assign(m, ident32);
+                        std::vector<uint32_t> least(m, ident32);
+                        for (size_t q = 0; q < end_slot; q++) {
+                            if (!((s_meta[q] >> kMetaDegShift) & 15u)) continue;
+                            const uint32_t r = s_meta[q] & 0xffffu, mag = enc32(s_lam32[q]) & 0x7fffffffu;
+                            o.row2[r] = std::min(o.row2[r], std::max(least[r], mag));
+                            least[r] = std::min(least[r], mag);
+                        }
+                    }
+                }
+                // the first group that keeps its states in the slab
+                // slots: least bytes over the sweep, 64 for a record that
+                // fits, 256 for states in the slots, and for a record
+                // that may not fit (expected count plus 2.5 standard
+                // deviations above 12) what the late load costs
+                uint32_t kd = nch;
+                double cost = 0.0, best = 0.0;
+                for (uint32_t k = nch; k-- > 0;) {
+                    const double ex = c_exp[k];
+                    cost += 256.0 - (ex + 2.5 * std::sqrt(ex) <= 12.0 ? 64.0 : 1024.0);
+                    if (k % 8 == 0 && cost < best) {
+                        best = cost;
+                        kd = k;
+                    }
+                }
+                o.dense0 = kd == nch ? ng : kd / 4;
+                o.kept = kd;
+            }
+        }
+        // interleave the schedule fields into chunk records
+        o.recs.resize(nchunks * rb);
+        for (size_t k = 0; k < nchunks; k++) {
+            unsigned char* r = o.recs.data() + k * rb;
+            std::memcpy(r, &s_meta[k * kWave], 4 * kWave);
+            std::memcpy(r + kRecV, &s_v[k * kWave], 4 * kWave);
+            std::memcpy(r + kRecLam, fp64 ? (const void*)&s_lam64[k * kWave] : (const void*)&s_lam32[k * kWave], fb * kWave);
+            std::memcpy(r + ri0, fp64 ? (const void*)&init64[k * kWave] : (const void*)&init32[k * kWave], fb * kWave);
+        }
+    };
+    std::vector<MemberSched> ms(layered ? 0u : c.L);  // the layered schedule has no chunks
+    if (!for_members<SchedScratch>((uint32_t)ms.size(), E * c.L,
+                                   [&](uint32_t i, SchedScratch& w) { member(i, w, ms[i]); }))
+        return fail(VIBE_ENOMEM, "host allocation failed");
+    std::vector<uint32_t> member_chunk(c.L + 1, 0), c_group(c.L + 1, 0), c_dense0(c.L, 0);
+    uint32_t lev_min = UINT32_MAX, lev_max = 0, ch_min = UINT32_MAX, ch_max = 0;
+    uint64_t nchunks = 0, c_chunks = 0;
+    for (uint32_t i = 0; i < ms.size(); i++) {
+        const MemberSched& o = ms[i];
+        if (!o.whole) return fail(VIBE_EINVAL, "internal: schedule does not cover every column");
+        lev_min = std::min(lev_min, o.levels);
+        lev_max = std::max(lev_max, o.levels);
+        ch_min = std::min(ch_min, o.chunks);
+        ch_max = std::max(ch_max, o.chunks);
+        nchunks += o.chunks;
+        if (nchunks * kWave >= (1ull << 32)) return fail(VIBE_EUNSUPPORTED, "schedules exceed 2^32 slots");
+        member_chunk[i + 1] = (uint32_t)nchunks;
+        c_group[i + 1] = c_group[i] + o.groups;
+        c_dense0[i] = o.dense0;
+        c_chunks += o.kept;
     }
-
+    if (ch_min == UINT32_MAX) ch_min = 0;
     vibe_graph* g = new (std::nothrow) vibe_graph();
     if (!g) return fail(VIBE_ENOMEM, "host allocation failed");
     GraphHost& h = g->h;
@@ -648,40 +719,40 @@ extern "C" int vibe_graph_create(uint32_t m, uint32_t n, const uint32_t* h_indpt
                 const uint32_t q = a - h_indptr[r];
                 l_cols[((size_t)r * 64 + q % 64) * NR + q / 64] = 4u * h_indices[a];
             }
-        // the checks that share a column with each check
-        std::vector<uint32_t> near, nptr(1, 0), mark(m, UINT32_MAX);
-        for (uint32_t r = 0; r < m; r++) {
-            mark[r] = r;
-            for (uint32_t a = h_indptr[r]; a < h_indptr[r + 1]; a++)
-                for (uint32_t j = cp[h_indices[a]]; j < cp[h_indices[a] + 1]; j++)
-                    if (mark[ci[j]] != r) {
-                        mark[ci[j]] = r;
-                        near.push_back(ci[j]);
-                    }
-            nptr.push_back((uint32_t)near.size());
-        }
-        // a check's level: one more than that of the checks before it in the
-        // member's order that share a column; two of a level share none.
-        // Levels count from 1: a check not yet met has level 0.
+        // One wavefront takes the checks in the member's order.  For more, a
+        // check's level: one more than that of the checks before it in the
+        // member's order that share a column, which is the highest so far on
+        // its columns; two of a level share none.  Levels count from 1.
+        struct Columns {
+            std::vector<uint32_t> level;
+        };
         std::vector<uint32_t> lev((size_t)c.L * m, 0);
         std::vector<std::vector<uint32_t>> first(c.L);  // first group of each level, then the end
-        for (uint32_t i = 0; i < c.L; i++) {
+        // (some 8 ns an edge, a fiftieth of what building a chunked schedule takes)
+        const bool ok = W == 1 || for_members<Columns>(c.L, E * c.L / 50, [&](uint32_t i, Columns& w) {
+            w.level.assign(n, 0);
             uint32_t* l = lev.data() + (size_t)i * m;
             std::vector<uint32_t> size(1, 0);
             for (uint32_t a = 0; a < m; a++) {
                 const uint32_t r = perms[(size_t)i * m + a];
                 uint32_t x = 0;
-                for (uint32_t b = nptr[r]; b < nptr[r + 1]; b++) x = std::max(x, l[near[b]]);
+                for (uint32_t b = h_indptr[r]; b < h_indptr[r + 1]; b++) x = std::max(x, w.level[h_indices[b]]);
+                for (uint32_t b = h_indptr[r]; b < h_indptr[r + 1]; b++) w.level[h_indices[b]] = x + 1;
                 l[r] = x + 1;
                 if (size.size() <= x) size.resize(x + 1, 0);
                 size[x]++;
             }
             first[i].assign(1, 0);
             for (uint32_t q : size) first[i].push_back(first[i].back() + (q + W - 1) / W);
-            d.lgroups = std::max(d.lgroups, first[i].back());
+        });
+        if (!ok) {
+            delete g;
+            return fail(VIBE_ENOMEM, "host allocation failed");
         }
+        for (uint32_t i = 0; i < c.L; i++) d.lgroups = std::max(d.lgroups, W == 1 ? m : first[i].back());
         l_order.assign((size_t)c.L * d.lgroups * W, m);
-        for (uint32_t i = 0; i < c.L; i++) {
+        if (W == 1) l_order.assign(perms, perms + (size_t)c.L * m);
+        for (uint32_t i = 0; W > 1 && i < c.L; i++) {
             for (uint32_t& f : first[i]) f *= W;
             for (uint32_t a = 0; a < m; a++) {
                 const uint32_t r = perms[(size_t)i * m + a];
@@ -742,22 +813,12 @@ extern "C" int vibe_graph_create(uint32_t m, uint32_t n, const uint32_t* h_indpt
             s_sched.push_back(bits);
         }
     }
-    // interleave the schedule fields into chunk records
-    const size_t nrec = s_meta.size() / kWave;
-    const uint32_t rb = rec_bytes(fp64), ri0 = rec_init(fp64);
-    std::vector<unsigned char> sched(nrec * rb);
-    for (size_t j = 0; j < nrec; j++) {
-        unsigned char* r = sched.data() + j * rb;
-        std::memcpy(r, &s_meta[j * kWave], 4 * kWave);
-        std::memcpy(r + kRecV, &s_v[j * kWave], 4 * kWave);
-        if (fp64) {
-            std::memcpy(r + kRecLam, &s_lam64[j * kWave], 8 * kWave);
-            std::memcpy(r + ri0, &init64[j * kWave], 8 * kWave);
-        } else {
-            std::memcpy(r + kRecLam, &s_lam32[j * kWave], 4 * kWave);
-            std::memcpy(r + ri0, &init32[j * kWave], 4 * kWave);
-        }
-    }
+    std::vector<unsigned char> sched(std::max<size_t>(nchunks, 1) * rb);
+    if (nchunks == 0)  // no edges at all: one (unused) record
+        for (uint32_t q = 0; q < (uint32_t)kWave; q++)
+            std::memcpy(&sched[ri0 + fb * q], fp64 ? (const void*)&ident64 : (const void*)&ident32, fb);
+    for (size_t i = 0; i < ms.size(); i++)
+        std::copy(ms[i].recs.begin(), ms[i].recs.end(), sched.begin() + (size_t)member_chunk[i] * rb);
     int rc = VIBE_OK;
     const float* lam32_d = nullptr;
     // Graphs of at least 16 chunks, where the padding to whole groups is
@@ -768,13 +829,21 @@ extern "C" int vibe_graph_create(uint32_t m, uint32_t n, const uint32_t* h_indpt
     // every second or third edge: where most chunks would not fit theirs,
     // all keep their states in the slab.
     //
-    // The slabs are streamed where those of 4096 wavefronts (16 on each of
-    // 256 CUs) exceed the 256 MB of the last-level cache: of 60 KB each they
-    // run in 4.87 ms, streamed 5.72; of 79 KB in 29.5 and 26.1.
+    // The slabs are streamed where the messages alone, 1 KB a group, of 4096
+    // wavefronts (16 on each of 256 CUs) exceed the 256 MB of the last-level
+    // cache: 60 KB each take 4.87 ms, streamed 5.72; 79 KB 29.5 and 26.1.
+    // That is decided here, for the graph, and so also for a launch whose few
+    // slabs would stay in the caches.
     auto compact_upload = [&]() -> int {
-        DevGraph v = d;
-        v.compact = 1;
-        if (!want_compact || ch_min < 16 || bp_lds_bytes(v, false) > 64 * 1024) return VIBE_OK;
+        if (!want_compact || ch_min < 16) return VIBE_OK;
+        std::vector<uint32_t> c_sched, c_rec0;
+        c_sched.reserve((size_t)c_group[c.L] * 512);
+        c_rec0.reserve((size_t)c_group[c.L] * 64);
+        for (MemberSched& o : ms) {
+            c_sched.insert(c_sched.end(), o.csched.begin(), o.csched.end());
+            c_rec0.insert(c_rec0.end(), o.crec0.begin(), o.crec0.end());
+        }
+        const std::vector<uint32_t>&c_row0 = ms[0].row0, &c_row2 = ms[0].row2;
         if (2 * c_chunks < member_chunk[c.L]) std::fill(c_dense0.begin(), c_dense0.end(), 0u);
         const uint32_t* p[2] = {nullptr, nullptr};
         int r;

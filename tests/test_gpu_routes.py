@@ -90,3 +90,24 @@ def test_thousands_of_checks_with_short_rows(torch_cuda):
     assert few
     rt.close()
     G.close()
+
+
+def test_members_are_built_side_by_side(torch_cuda):
+    """Creating a graph of 32 members takes less than half of 32 graphs of one
+    member (one after the other: three quarters)."""
+    import paper_2508_15743_amd as P
+
+    dem = circuit_dem(5, 5, 1e-3)
+
+    def create(L):
+        perms, best = permutations(dem.n, L, 1), 1e9
+        for _ in range(5):
+            t = time.perf_counter()
+            G = P.Graph.from_dem(dem, perms, L=L, M=1, T_max=20)
+            best = min(best, time.perf_counter() - t)
+            G.close()
+        return best * 1e3
+
+    one, all_ = create(1), create(32)
+    print(f"one member {one:.2f} ms, 32 members {all_:.2f} ms", flush=True)
+    assert all_ <= 16 * one
