@@ -829,7 +829,9 @@ __device__ __forceinline__ void run_item(const DevGraph& g, const BpLaunch& a, u
 
     uint32_t conv_t = 0, ran = 0;
     bool stopped = false;
-    uint64_t sat = 0;  // lanes that saw a posterior or message reach the clamp (saturation witness)
+    // lanes that saw a posterior or message reach the clamp (saturation
+    // witness), as each lane knows it: those that sat a step out do not
+    uint64_t sat = 0;
     for (uint32_t t = 1; t <= a.T_run; t++) {
         if (a.use_M && t >= 2 && preceding_converged(cmask, t, mem, lane) >= g.M) {
             stopped = true;  // cannot be among the first M any more
@@ -873,7 +875,7 @@ __device__ __forceinline__ void run_item(const DevGraph& g, const BpLaunch& a, u
         }
     }
 
-    finish_item<F, DG>(g, a, shot, mem, conv_t, ran, stopped, uni(sat != 0 ? 1u : 0u) != 0, eb, post, lane);
+    finish_item<F, DG>(g, a, shot, mem, conv_t, ran, stopped, __ballot(sat != 0) != 0, eb, post, lane);
 }
 
 // One work item of the multi-shot launch: member mem on the P shots

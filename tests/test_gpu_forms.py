@@ -74,6 +74,39 @@ def test_saturation_mark_of_the_compact_bodies(torch_cuda, key):
     assert min(marks) > 0
 
 
+def test_saturation_mark_of_layered_forms(torch_cuda):
+    """A row of one check raises its column to alpha x clamp; columns 0 to 9
+    are in no check.  Posteriors in LDS, in global memory (a ragged round) and
+    in FP64, against the oracle."""
+    import paper_2508_15743_amd as P
+    from oracle import oracle as O
+
+    torch = torch_cuda
+    h = np.zeros((12, 38), np.uint8)
+    for r in range(12):
+        h[r, 10 + 2 * r:12 + 2 * r + (r % 3)] = 1
+    h[5] = 0
+    h[5, 37] = 1
+    dem = dem_from_dense(h, np.full(38, 0.01), np.ones((1, 38), np.uint8))
+    perms = permutations(12, 4, 5)
+    synd = sample(dem, 40, 6).syndromes
+    synd[:, 0] = 1
+    s = torch.from_numpy(synd).to("cuda:0")
+    kw = dict(L=4, M=1, T_max=3, alpha=1.25, schedule="layered")
+    G, G64 = P.Graph.from_dem(dem, perms, **kw), P.Graph.from_dem(dem, perms, message_bits=64, **kw)
+    rt = P.Runtime()
+    forms = {"LDS": G.decode(s), "ragged": rt.decode([(G, s)])[0], "FP64": G64.decode(s), "FP64 ragged": rt.decode([(G64, s)])[0]}
+    flags = {k: (o[2][:, 0] & P.FLAG_SATURATED).cpu().numpy() for k, o in forms.items()}
+    ref = O.decode(O.OracleGraph(dem), perms, synd, L=4, M=1, T=3, alpha=1.25, schedule="layered")
+    want = ref["saturated"] * P.FLAG_SATURATED
+    print({k: int((f != 0).sum()) for k, f in flags.items()}, int((want != 0).sum()), flush=True)
+    for k, f in flags.items():
+        assert np.array_equal(f, want), k
+    rt.close()
+    G.close()
+    G64.close()
+
+
 def test_forms_of_the_general_body(torch_cuda):
     """Columns of 9 to 15 checks in FP32: every chunk on the general body, in
     its persistent and latency forms, decisions in LDS and in global memory,
