@@ -52,7 +52,7 @@ HBM_PEAK_GBS = 8000.0  # MI355X HBM3E, GB/s
 BYTES_PER_EDGE_UPDATE = 8.0
 
 
-PROFILE = os.path.join(ROOT, "profiles", "bp_ensemble_kernel_circuit_d9_r9_p1e-3.txt")
+PROFILE = os.path.join(ROOT, "profiles", "bp_compact_kernel_circuit_d9_r9_p1e-3.txt")
 KERNEL_SOURCES = ("bp.hip", "bp_compact.h", "bp_small.h", "bp_layered.h", "internal.h", "graph.hip")
 GRAD_PROFILE = os.path.join(ROOT, "profiles", "bp_grad_kernel_circuit_d5_r5_p1e-3.txt")
 GRAD_SOURCES = ("grad.hip", "internal.h", "graph.hip")
@@ -580,15 +580,17 @@ def main():
     bp_s = bp_ms / 1e3
     achieved = BYTES_PER_EDGE_UPDATE * edge_updates / bp_s / 1e9 if bp_s > 0 else 0.0
     launch_shots = max(1, B // max(1, bp_launches // args.steps))
+    # the workload's graph has compact data: one shot per wavefront runs it
+    kernel = ("bp_multi_kernel" if tune["shots_per_wave"] > 1
+              else "bp_ensemble_kernel" if tune["slab_in_lds"] else "bp_compact_kernel")
     roofline = {"bound": "hbm", "achieved": round(achieved, 2), "peak": HBM_PEAK_GBS, "unit": "GB/s",
                 "frac": round(achieved / HBM_PEAK_GBS, 4),
                 "measured_peak": round(copy_gbs, 1), "frac_of_measured": round(achieved / copy_gbs, 4),
                 # the committed counters were taken with the default settings:
-                # one shot per wavefront, decisions in LDS
-                "traffic": (measured_traffic(launch_shots)
-                            if tune["shots_per_wave"] == 1 and tune["decisions_global"] != 1 else None),
+                # one shot per wavefront, the slab in global memory
+                "traffic": measured_traffic(launch_shots) if kernel == "bp_compact_kernel" else None,
                 "slab_stream_ceiling": round(stream_gbs, 1),
-                "kernel": "bp_ensemble_kernel",
+                "kernel": kernel,
                 "avg_launch_ms": round(bp_ms / max(bp_launches, 1), 3),
                 "edge_updates_per_s": edge_updates / bp_s if bp_s > 0 else 0.0,
                 "kernel_ms": {k: round(v[0], 2) for k, v in prof.items()}}

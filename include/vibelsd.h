@@ -333,10 +333,12 @@ void vibe_exec_destroy(vibe_exec* ex); /* synchronises the device first; NULL ac
  *                   than reside with the bitmap in LDS (a small batch is
  *                   bound by its serial chains, which the global masks
  *                   lengthen).  Not with the slab in LDS.  FP32 graphs on
- *                   the serial schedule whose rows are long run an item
- *                   body with one row state per check and a mask of
- *                   decisions per chunk (one shot per wavefront, slab in
- *                   global memory): there this setting changes nothing.
+ *                   the serial or parallel schedule with columns of at most
+ *                   8 checks, fewer than 8192 checks and at least 16 chunks
+ *                   run an item body with row states per check and a mask
+ *                   of decisions per chunk (one shot per wavefront, slab in
+ *                   global memory), and small graphs in large batches one
+ *                   lane per shot: there this setting changes nothing.
  * A launch whose work items all reside at once (no more than the grid)
  * runs a variant that loads more chunks ahead at fewer wavefronts per SIMD
  * (FP32, serial schedule, slab in global memory, one shot per wavefront,

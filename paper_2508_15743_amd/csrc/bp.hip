@@ -34,10 +34,10 @@
 // in global memory: a mask per chunk read with the chunk's slots, and a
 // bitmap updated on flips); convergence is a ballot.
 //
-// Launch variants (none changes a result): compact suffix states, the FP32
-// item body of graphs whose rows are long (bp_compact.h); the slab in LDS
-// for small graphs; P = 2 or 4 shots of a member per wavefront on the member's
-// schedule recut into chunks of 64 / P edges; several requests on
+// Launch variants (none changes a result): row states per check, the FP32
+// item body of chunked schedules of 16 chunks and more (bp_compact.h); the
+// slab in LDS for small graphs; P = 2 or 4 shots of a member per wavefront on
+// the member's schedule recut into chunks of 64 / P edges; several requests on
 // different graphs in one persistent launch (ragged); and, for a launch
 // whose items all reside at once, the deeper prefetch ring at four waves
 // per SIMD (the latency variant).

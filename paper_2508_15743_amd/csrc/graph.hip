@@ -836,25 +836,27 @@ extern "C" int vibe_graph_create(uint32_t m, uint32_t n, const uint32_t* h_indpt
     // slabs would stay in the caches.
     auto compact_upload = [&]() -> int {
         if (!want_compact || ch_min < 16) return VIBE_OK;
-        std::vector<uint32_t> c_sched, c_rec0;
-        c_sched.reserve((size_t)c_group[c.L] * 512);
-        c_rec0.reserve((size_t)c_group[c.L] * 64);
-        for (MemberSched& o : ms) {
-            c_sched.insert(c_sched.end(), o.csched.begin(), o.csched.end());
-            c_rec0.insert(c_rec0.end(), o.crec0.begin(), o.crec0.end());
-        }
-        const std::vector<uint32_t>&c_row0 = ms[0].row0, &c_row2 = ms[0].row2;
         if (2 * c_chunks < member_chunk[c.L]) std::fill(c_dense0.begin(), c_dense0.end(), 0u);
-        const uint32_t* p[2] = {nullptr, nullptr};
-        int r;
-        if ((r = upload(h, c_rec0.data(), c_rec0.size(), &p[0])) || (r = upload(h, c_row0.data(), c_row0.size(), &d.crow0)) ||
-            (r = upload(h, c_row2.data(), c_row2.size(), &d.crow2)) ||
-            (r = upload(h, c_group.data(), c_group.size(), &d.cgroup)) ||
-            (r = upload(h, c_dense0.data(), c_dense0.size(), &d.dense0)) ||
-            (r = upload(h, c_sched.data(), c_sched.size(), &p[1])))
-            return r;
-        d.crec0 = reinterpret_cast<const unsigned char*>(p[0]);
-        d.csched = reinterpret_cast<const unsigned char*>(p[1]);
+        // one allocation: the schedule, the records, then the small arrays
+        const size_t groups = c_group[c.L];
+        std::vector<uint32_t> all;
+        all.reserve(groups * (512 + 64) + 2 * (size_t)m + 2 * c.L + 4 * 64 + 1);
+        for (MemberSched& o : ms) all.insert(all.end(), o.csched.begin(), o.csched.end());
+        for (MemberSched& o : ms) all.insert(all.end(), o.crec0.begin(), o.crec0.end());
+        size_t at[4], i4 = 0;
+        for (const std::vector<uint32_t>* v : {&ms[0].row0, &ms[0].row2, &c_group, &c_dense0}) {
+            all.resize((all.size() + 63) / 64 * 64);
+            at[i4++] = all.size();
+            all.insert(all.end(), v->begin(), v->end());
+        }
+        const uint32_t* p = nullptr;
+        if (int r = upload(h, all.data(), all.size(), &p)) return r;
+        d.csched = reinterpret_cast<const unsigned char*>(p);
+        d.crec0 = reinterpret_cast<const unsigned char*>(p + groups * 512);
+        d.crow0 = p + at[0];
+        d.crow2 = p + at[1];
+        d.cgroup = p + at[2];
+        d.dense0 = p + at[3];
         for (uint32_t i = 0; i < c.L; i++) d.cgroups = std::max(d.cgroups, c_group[i + 1] - c_group[i]);
         if (d.cgroups > 64) d.ccols |= kCompactStream;
         return VIBE_OK;
