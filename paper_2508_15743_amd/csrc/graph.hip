@@ -728,8 +728,8 @@ extern "C" int vibe_graph_create(uint32_t m, uint32_t n, const uint32_t* h_indpt
         };
         std::vector<uint32_t> lev((size_t)c.L * m, 0);
         std::vector<std::vector<uint32_t>> first(c.L);  // first group of each level, then the end
-        // (some 8 ns an edge, a fiftieth of what building a chunked schedule takes)
-        const bool ok = W == 1 || for_members<Columns>(c.L, E * c.L / 50, [&](uint32_t i, Columns& w) {
+        // (some 3 to 8 ns an edge; building a chunked schedule takes 50 times that)
+        const bool ok = W == 1 || for_members<Columns>(c.L, E * c.L / 16, [&](uint32_t i, Columns& w) {
             w.level.assign(n, 0);
             uint32_t* l = lev.data() + (size_t)i * m;
             std::vector<uint32_t> size(1, 0);
