@@ -83,6 +83,8 @@ __global__ __launch_bounds__(kWave) void bp_small_kernel(DevGraph g, BpLaunch a)
     CWord* lam_e = (CWord*)(g.ssched + (size_t)g.L * g.scols * CWD);
     // fewer than M other members never stop one
     const bool limited = a.use_M && g.M < g.L;
+    const uint64_t e0 = g.e0[0];
+    const float alpha = (float)g.alpha;
     *lds_at(g.E * 256u + lane4) = g.ident32;
     // The wavefront's member, or members where there are fewer wavefronts, and
     // its share of the shots: those of a member are split evenly over the
@@ -210,9 +212,9 @@ __global__ __launch_bounds__(kWave) void bp_small_kernel(DevGraph g, BpLaunch a)
             if (!busy) break;
             const bool act = (busy >> lane) & 1ull, ends = act && t == a.T_run;
             uint64_t* cmask = a.conv_mask + (size_t)shot * (kMaxT + 1);
-            const float al = g.alpha_t ? (float)g.alpha_t[t - 1] : (float)g.alpha;
+            const float al = g.alpha_t ? (float)g.alpha_t[t - 1] : alpha;
             const bool want_post = __ballot(ends) != 0;
-            uint64_t e = g.e0[0], res = s;
+            uint64_t e = e0, res = s;
             for (uint32_t q = 0; q < g.scols; q++) {
                 CWord* w = cols + (size_t)q * CWD;
                 uint32_t wd[CWD];
